@@ -1,6 +1,7 @@
 // context.hip -- host runtime behind the C ABI of include/lbm.h: validation,
 // all-or-nothing allocation, the tile chooser, per-step launch bookkeeping,
 // cached HIP graphs of K-update bundles, readouts and FP64 diagnostics.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -77,10 +78,13 @@ struct lbm_ctx {
     double* dout = nullptr;
     int64_t lat_elems = 0, edge_elems = 0;
     int64_t t = 0;
+    int cur = 0;    // two-lattice schemes: the lattice that holds the state
+    FusedPlan plan; // several updates per launch
     int32_t bundle = 32;
     int32_t block = 256;
     hipGraph_t graph[2] = {nullptr, nullptr};
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
+    int graph_cur[2] = {0, 0}; // the lattice that holds the state after each graph
     bool have_prev = false;
     bool poisoned = false;
     std::string err;
@@ -99,10 +103,10 @@ struct lbm_ctx {
         if (e == hipSuccess) return LBM_OK;
         return fail(LBM_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
     }
-    void* cur_lat() const { return is_two_lattice(grid.scheme) ? lat[t & 1] : lat[0]; }
+    void* cur_lat() const { return lat[cur]; }
     // State kind of the current lattice: AA alternates push (even t) and swap (odd t).
     int state_now() const { return grid.scheme == S_AA ? ((t & 1) ? ST_SWAP : ST_PUSH) : state; }
-    void* other_lat() const { return is_two_lattice(grid.scheme) ? lat[(t + 1) & 1] : nullptr; }
+    void* other_lat() const { return lat[cur ^ 1]; }
     // Kernel parameters of the update of the given parity (update: it records
     // the Neumann inlet densities for the next one) or of a readout.
     KParams at(int parity, bool update) const
@@ -251,27 +255,56 @@ lbm_status alloc(lbm_ctx* c, void** p, size_t bytes)
     return LBM_OK;
 }
 
-lbm_status launch_one(lbm_ctx* c, int parity, hipStream_t s)
+// The one update after update count t (its parity is what matters), state in
+// lattice cur.
+lbm_status launch_one(lbm_ctx* c, int parity, int cur, hipStream_t s)
 {
     const KParams p = c->at(parity, true);
     hipError_t e;
     if (c->grid.scheme == S_AA)
         e = launch_aa(c->grid.layout, c->grid.precision, p, parity, c->lat[0], c->obuf, s);
     else if (is_two_lattice(c->grid.scheme))
-        e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, c->lat[parity],
-                          c->lat[parity ^ 1], nullptr, nullptr, s);
+        e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, c->lat[cur],
+                          c->lat[cur ^ 1], nullptr, nullptr, s);
     else
         e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, nullptr, c->lat[0],
                           c->edge[parity], c->edge[parity ^ 1], s);
     return c->check(e, "update launch");
 }
 
-lbm_status build_graph(lbm_ctx* c, int parity)
+// n updates on stream s from update count t on, the state in lattice cur
+// (cur moves along): in as few launches as `most` updates per launch allow,
+// evenly filled.
+lbm_status launch_updates(lbm_ctx* c, int64_t t, int64_t n, int most, int& cur, hipStream_t s)
+{
+    const bool two = is_two_lattice(c->grid.scheme);
+    for (int64_t left = n; left > 0;) {
+        const int64_t launches = (left + most - 1) / most;
+        const int kk = (int)((left + launches - 1) / launches);
+        lbm_status st;
+        if (kk == 1)
+            st = launch_one(c, (int)((t + n - left) & 1), cur, s);
+        else
+            st = c->check(launch_fused(c->grid.scheme, c->grid.layout, c->grid.precision, c->kp, c->plan, kk,
+                                       c->lat[cur], c->lat[cur ^ 1], s),
+                          "update launch");
+        if (st != LBM_OK) return st;
+        if (two) cur ^= 1;
+        left -= kk;
+    }
+    return LBM_OK;
+}
+
+// Which cached graph serves the next bundle: a graph holds the lattices it
+// was captured with (two-lattice schemes) or starts at one update parity.
+int graph_key(const lbm_ctx* c) { return is_two_lattice(c->grid.scheme) ? c->cur : (int)(c->t & 1); }
+
+lbm_status build_graph(lbm_ctx* c, int key)
 {
     hipError_t e = hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return c->check(e, "hipStreamBeginCapture");
-    lbm_status st = LBM_OK;
-    for (int k = 0; k < c->bundle && st == LBM_OK; ++k) st = launch_one(c, (parity + k) & 1, c->cap);
+    int cur = c->cur;
+    const lbm_status st = launch_updates(c, c->t, c->bundle, c->plan.kk, cur, c->cap);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(c->cap, &g);
     if (st != LBM_OK) {
@@ -285,8 +318,9 @@ lbm_status build_graph(lbm_ctx* c, int parity)
         (void)hipGraphDestroy(g);
         return c->check(e, "hipGraphInstantiate");
     }
-    c->graph[parity] = g;
-    c->gexec[parity] = x;
+    c->graph[key] = g;
+    c->gexec[key] = x;
+    c->graph_cur[key] = cur;
     return LBM_OK;
 }
 
@@ -554,6 +588,7 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     }
     c->block = grid->scheme == LBM_LPTL ? lptl_block_size(grid->layout, grid->precision)
                                         : (g.tx / g.vx) * g.ty;
+    if (!c->rin) c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
     *out = c;
     return LBM_OK;
 }
@@ -563,23 +598,22 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    while (n > 0) {
-        const int parity = (int)(c->t & 1);
-        if (c->bundle > 0 && n >= c->bundle) {
-            if (!c->gexec[parity]) {
-                lbm_status st = build_graph(c, parity);
-                if (st != LBM_OK) return st;
-            }
-            lbm_status st = c->check(hipGraphLaunch(c->gexec[parity], c->stream), "hipGraphLaunch");
+    while (c->bundle > 0 && n >= c->bundle) {
+        const int key = graph_key(c);
+        if (!c->gexec[key]) {
+            lbm_status st = build_graph(c, key);
             if (st != LBM_OK) return st;
-            c->t += c->bundle;
-            n -= c->bundle;
-        } else {
-            lbm_status st = launch_one(c, parity, c->stream);
-            if (st != LBM_OK) return st;
-            c->t += 1;
-            n -= 1;
         }
+        lbm_status st = c->check(hipGraphLaunch(c->gexec[key], c->stream), "hipGraphLaunch");
+        if (st != LBM_OK) return st;
+        c->cur = c->graph_cur[key];
+        c->t += c->bundle;
+        n -= c->bundle;
+    }
+    if (n > 0) {
+        lbm_status st = launch_updates(c, c->t, n, c->bundle > 0 ? c->plan.kk : 1, c->cur, c->stream);
+        if (st != LBM_OK) return st;
+        c->t += n;
     }
     return LBM_OK;
 }

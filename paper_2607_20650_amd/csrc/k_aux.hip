@@ -59,16 +59,13 @@ __global__ void k_links(Geometry g, const uint8_t* __restrict__ types, uint32_t*
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= g.px * g.ny) return;
     const int64_t y = m / g.px, x = m - y * g.px;
-    uint32_t w = 0;
+    uint32_t w = x < g.nx ? 0 : LINK_NONE;
     if (x < g.nx) {
         for (int i = 0; i < 9; ++i) {
             const int64_t sx = x - dir_cx(i), sy = y - dir_cy(i);
             const bool wrap = ((sy < 0 || sy >= g.ny) && g.ya == AX_PERIODIC) ||
                               ((sx < 0 || sx >= g.nx) && g.xa == AX_PERIODIC);
-            if (wrap) {
-                w |= LINK_GENERAL;
-                continue;
-            }
+            if (wrap) w |= LINK_GENERAL;
             int64_t sn = 0;
             const int k = pull_source(g, types, x, y, i, sn, g.fw != 0);
             uint32_t kind = LINK_PLAIN;
@@ -76,10 +73,11 @@ __global__ void k_links(Geometry g, const uint8_t* __restrict__ types, uint32_t*
                 kind = LINK_SOLID;
             else if (k == K_INLET)
                 kind = LINK_INLET;
-            else if (sx >= g.nx)
+            else if (sx >= g.nx && g.xa == AX_INOUT)
                 kind = LINK_CLAMP; // the outlet's zero-gradient source
             w |= kind << (2 * i);
         }
+        if (!updated(types[m])) w |= LINK_NONE;
     }
     links[m] = w;
 }

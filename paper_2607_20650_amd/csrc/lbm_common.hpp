@@ -59,8 +59,9 @@ struct KParams {
     const float* rin;
     float* rout;
     // Source kinds of every node's pull, 2 bits per direction i at bits 2i
-    // (LINK_* below), bit 31 set where a source lies across a periodic side;
-    // null in readouts.
+    // (LINK_* below; a source across a periodic side has the kind of the
+    // wrapped node), bit 31 set where a source lies across a periodic side,
+    // bit 30 where the node is not updated; 0 for every regular node.
     const uint32_t* links;
 };
 
@@ -72,6 +73,7 @@ enum LinkKind : uint32_t {
     LINK_CLAMP = 3  // past the outlet: the outlet node (x, y - c_y) (zero gradient)
 };
 constexpr uint32_t LINK_GENERAL = 0x80000000u; // a source across a periodic side
+constexpr uint32_t LINK_NONE = 0x40000000u;    // the node is not updated (solid or inlet)
 
 // Edge-buffer ("buffer grid") extents of the one-lattice schemes, per parity:
 // X edges hold, per tile column, 2 sides x 3 values (c_y+1) x every row of

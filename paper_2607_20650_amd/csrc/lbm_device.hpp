@@ -335,8 +335,10 @@ __device__ __forceinline__ float c_dot(float jx, float jy)
         return Y > 0 ? jy : -jy;
     else if constexpr (Y == 0)
         return X > 0 ? jx : -jx;
+    else if constexpr (X == Y) // -(jx + jy) and -(jx - jy) are exact negations: one sum, one difference
+        return X > 0 ? jx + jy : -(jx + jy);
     else
-        return (X > 0 ? jx : -jx) + (Y > 0 ? jy : -jy);
+        return X > 0 ? jx - jy : -(jx - jy);
 }
 
 template <int I>

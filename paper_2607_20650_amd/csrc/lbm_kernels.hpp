@@ -10,6 +10,17 @@ namespace lbm {
 hipError_t launch_update(int scheme, int layout, int prec, const KParams& p, int block, const void* src, void* dst,
                          const void* ein, void* eout, hipStream_t s);
 
+// How a two-lattice simulation runs several updates per launch.
+struct FusedPlan {
+    int kk = 1;   // most updates per launch; 1: single updates only
+    int tile = 0; // tiles of one node per thread instead of marching strips
+    int rows = 0; // strips: rows per block
+};
+FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec);
+// kk updates (1 .. q.kk) in one launch, src -> dst.
+hipError_t launch_fused(int scheme, int layout, int prec, const KParams& p, const FusedPlan& q, int kk, const void* src,
+                        void* dst, hipStream_t s);
+
 // One AA update in place on lat.  parity 0: even update (local; push state
 // -> swap state; also writes the outlet side buffer obuf, 3 values per row,
 // when the x axis is inflow/outflow).  parity 1: odd update (pairwise

@@ -1,0 +1,60 @@
+"""Several updates per launch against single updates, bitwise.
+
+With ``bundle=0`` every update is a launch of the scheme's own kernel; the
+default runs several updates per launch (tiles on small grids, marching strips
+on large ones).  Both do the same operations per node in the same order, so
+every population must be equal bit for bit, on grids that end inside a tile, a
+strip, a block of strips or a chunk of rows, on every boundary kind.
+"""
+import numpy as np
+import pytest
+
+from oracle import CLOSED, INFLOW_OUTFLOW, INFLOW_PRESSURE, NEUMANN_OUTFLOW, PERIODIC
+from paper_2607_20650_amd import workloads as W
+from tests.helpers import ALL_LAYOUTS, ALL_PRECISIONS
+
+pytestmark = pytest.mark.gpu
+
+AXES = [(PERIODIC, PERIODIC), (CLOSED, CLOSED), (INFLOW_OUTFLOW, CLOSED), (INFLOW_PRESSURE, PERIODIC),
+        (CLOSED, PERIODIC), (PERIODIC, CLOSED), (NEUMANN_OUTFLOW, CLOSED)]
+
+
+def _run(sim_cls, nx, ny, xa, ya, bundle, calls, **kw):
+    flags = W.random_flags(nx, ny, 0.1, nx + ny)
+    st = W.random_state(nx, ny, 0.02, 3, dtype=np.float32)
+    with sim_cls(flags, 0.8, xa, ya, u_in=(0.05, 0.01), g=(1e-4, 2e-4), u0=(0.02, 0.0), bundle=bundle, **kw) as sim:
+        sim.set_state(st)
+        for n in calls:
+            sim.step(n)
+        return sim.populations()
+
+
+def _compare(nx, ny, axes, schemes, layouts, precisions, calls=(4, 7, 1, 19, 3, 2)):
+    from paper_2607_20650_amd.lbm import Simulation
+    for xa, ya in axes:
+        if xa >= INFLOW_OUTFLOW and nx < 2:
+            continue
+        for scheme in schemes:
+            for layout in layouts:
+                for prec in precisions:
+                    kw = dict(scheme=scheme, layout=layout, precision=prec)
+                    a = _run(Simulation, nx, ny, xa, ya, 0, calls, **kw)
+                    b = _run(Simulation, nx, ny, xa, ya, 16, calls, **kw)
+                    assert np.array_equal(a, b, equal_nan=True), (nx, ny, xa, ya, kw, np.argwhere(a != b)[:3])
+
+
+@pytest.mark.parametrize("precision", ALL_PRECISIONS)
+@pytest.mark.parametrize("nx,ny", [(128, 64), (37, 20), (5, 3), (1, 7), (2, 2), (50, 33), (57, 5), (200, 101)])
+def test_small_grids_bitwise(nx, ny, precision):
+    _compare(nx, ny, AXES, ["NPTL", "PUSH"], ALL_LAYOUTS, [precision])
+
+
+@pytest.mark.parametrize("precision", ALL_PRECISIONS)
+@pytest.mark.parametrize("nx,ny", [(1009, 701), (193, 3700), (90001, 8), (180000, 4), (13, 60001)])
+def test_large_grids_bitwise(nx, ny, precision):
+    _compare(nx, ny, AXES[:4], ["NPTL", "PUSH"], ["stream"], [precision], calls=(8, 5, 17))
+
+
+def test_large_grid_layouts_bitwise():
+    _compare(1011, 707, AXES[2:4], ["LPTL", "NPTL", "PUSH"], ["bundle", "collision"], ["fp32", "fp16sr", "fp16c"],
+             calls=(8, 5))
