@@ -266,20 +266,64 @@ hipError_t launch_edge_fill(int state, int layout, int prec, const KParams& p, c
 }
 
 // ---------------------------------------------------------------- readouts
+// Row and column of dense node index m (a 32-bit division where it serves).
+__device__ __forceinline__ void split_index(const Geometry& g, int64_t m, int64_t& x, int64_t& y)
+{
+    if (g.nx * g.ny <= 0xffffffffll) {
+        const uint32_t q = (uint32_t)m / (uint32_t)g.nx;
+        y = q;
+        x = (uint32_t)m - q * (uint32_t)g.nx;
+    } else {
+        y = m / g.nx;
+        x = m - y * g.nx;
+    }
+}
+
+// Incoming populations of an updated node of type t: regular nodes read fixed
+// offsets and irregular ones their link word, as in the update kernels; only
+// sources across a periodic side look up neighbour types.  Reading every node
+// by its neighbours' types took 569 us for the fields of an 8192 x 4096 grid.
+template <int L, int S, class T>
+__device__ __forceinline__ void gather_typed(const KParams& p, const T* __restrict__ lat, int64_t x, int64_t y,
+                                             int64_t n, uint8_t t, float* f)
+{
+    if (!(t & IRREGULAR)) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const int64_t sn = S == ST_PUSH ? n : n - dir_cx(i) - dir_cy(i) * p.g.px;
+            f[i] = ld(lat[lat_at<L>(S == ST_PUSH ? i : post_slot<S>(i), sn, p.g.P)]);
+        }
+        return;
+    }
+    const uint32_t lk = p.links[n];
+    if (lk & LINK_GENERAL)
+        gather_state<L, S>(p, lat, x, y, n, f);
+    else if constexpr (S == ST_PUSH)
+        gather_push_linked<L>(p, lat, x, y, n, lk, f);
+    else
+        gather_linked<L, S, T>(p, lat, x, y, n, lk, f);
+}
+
 template <int S, int L, class T>
 __global__ void k_get_pop(KParams p, const T* __restrict__ lat, float* __restrict__ out)
 {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t N = p.g.nx * p.g.ny;
     if (m >= N) return;
-    const int64_t y = m / p.g.nx, x = m - y * p.g.nx;
+    int64_t x, y;
+    split_index(p.g, m, x, y);
     const int64_t n = y * p.g.px + x;
     const uint8_t t = p.types[n];
-    const bool upd = updated(t), inlet = node_type(t) == T_INLET;
     float f[9];
-    gather_state<L, S>(p, lat, x, y, upd ? n : 0, f); // in-bounds for every node
+    if (updated(t)) {
+        gather_typed<L, S>(p, lat, x, y, n, t, f);
+    } else {
+        const bool inlet = node_type(t) == T_INLET;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) out[i * N + m] = upd ? f[i] : (inlet ? inlet_node_value(p, i, y) : 0.0f);
+        for (int i = 0; i < 9; ++i) f[i] = inlet ? inlet_node_value(p, i, y) : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) out[i * N + m] = f[i];
 }
 
 hipError_t launch_get_populations(int state, int layout, int prec, const KParams& p, const void* lat, float* f,
@@ -299,13 +343,14 @@ __global__ void k_macros(KParams p, const T* __restrict__ lat, float* __restrict
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t N = p.g.nx * p.g.ny;
     if (m >= N) return;
-    const int64_t y = m / p.g.nx, x = m - y * p.g.nx;
+    int64_t x, y;
+    split_index(p.g, m, x, y);
     const int64_t n = y * p.g.px + x;
     const uint8_t t = p.types[n];
     float r = 0.0f, ux = 0.0f, uy = 0.0f;
     if (updated(t)) {
         float f[9];
-        gather_state<L, S>(p, lat, x, y, n, f);
+        gather_typed<L, S>(p, lat, x, y, n, t, f);
         float rt, jx, jy;
         moments(f, rt, jx, jy);
         r = 1.0f + rt;
@@ -364,11 +409,13 @@ __global__ void __launch_bounds__(DIAG_THREADS)
     const int64_t N = p.g.nx * p.g.ny;
     double acc[DIAG_VALUES] = {0, 0, 0, 0, 0};
     for (int64_t m = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x; m < N; m += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
-        const int64_t y = m / p.g.nx, x = m - y * p.g.nx;
+        int64_t x, y;
+        split_index(p.g, m, x, y);
         const int64_t n = y * p.g.px + x;
-        if (!updated(p.types[n])) continue;
+        const uint8_t t = p.types[n];
+        if (!updated(t)) continue;
         float f[9];
-        gather_state<L, S>(p, lat, x, y, n, f);
+        gather_typed<L, S>(p, lat, x, y, n, t, f);
         double r = 1.0, jx = 0.0, jy = 0.0;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {

@@ -1046,19 +1046,65 @@ template <int L, class T> __global__ void k3_aa_outlet_fill(KParams3 p, const T*
 }
 
 // ------------------------------------------------------------------ readouts
+// Coordinates of dense node index m (32-bit divisions where they serve).
+__device__ __forceinline__ void split_index3(const Geometry3& g, int64_t m, int64_t& x, int64_t& y, int64_t& z)
+{
+    if (g.nx * g.ny * g.nz <= 0xffffffffll) {
+        const uint32_t yz = (uint32_t)m / (uint32_t)g.nx, q = yz / (uint32_t)g.ny;
+        x = (uint32_t)m - yz * (uint32_t)g.nx;
+        y = yz - q * (uint32_t)g.ny;
+        z = q;
+    } else {
+        const int64_t yz = m / g.nx;
+        x = m - yz * g.nx;
+        z = yz / g.ny;
+        y = yz - z * g.ny;
+    }
+}
+
+// Incoming populations of an updated node of type t: regular nodes read fixed
+// (or, on a periodic border, wrapped) offsets, irregular ones look up their
+// neighbours' types.  Looking them up for every node took 590 us for the
+// fields of a 256^3 grid.
+template <int L, int S, class T>
+__device__ __forceinline__ void gather_typed3(const KParams3& p, const T* __restrict__ lat, int64_t x, int64_t y,
+                                              int64_t z, int64_t n, uint8_t t, float* f)
+{
+    if (t & IRREGULAR) {
+        gather_state3<L, S>(p, lat, x, y, z, n, f);
+    } else if constexpr (S == ST_PUSH) {
+#pragma unroll
+        for (int i = 0; i < Q3; ++i) f[i] = ld(lat[lat3<L>(i, n, p.g.P)]);
+    } else if (!__any(on_border(p.g, x, y, z))) {
+#pragma unroll
+        for (int i = 0; i < Q3; ++i) f[i] = ld(lat[lat3<L>(post_slot3<S>(i), n - q3_off(p.g, i), p.g.P)]);
+    } else { // a wavefront with nodes on a periodic border
+        const Wrap3 w = wrap_of(p.g, x, y, z);
+#pragma unroll
+        for (int i = 0; i < Q3; ++i)
+            f[i] = ld(lat[lat3<L>(post_slot3<S>(i), n + wrapped_off<-1>(p.g, w, i), p.g.P)]);
+    }
+}
+
 template <int S, int L, class T> __global__ void k3_get_pop(KParams3 p, const T* __restrict__ lat, float* __restrict__ out)
 {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t N = p.g.nx * p.g.ny * p.g.nz;
     if (m >= N) return;
-    const int64_t x = m % p.g.nx, yz = m / p.g.nx, y = yz % p.g.ny, z = yz / p.g.ny;
-    const int64_t n = yz * p.g.px + x;
+    int64_t x, y, z;
+    split_index3(p.g, m, x, y, z);
+    const int64_t n = (z * p.g.ny + y) * p.g.px + x;
     const uint8_t t = p.types[n];
-    const bool upd = updated(t), inlet = node_type(t) == T_INLET;
     float f[Q3];
-    gather_state3<L, S>(p, lat, x, y, z, upd ? n : 0, f); // in-bounds for every node
+    if (updated(t)) {
+        gather_typed3<L, S>(p, lat, x, y, z, n, t, f);
+    } else {
+        const bool inlet = node_type(t) == T_INLET;
 #pragma unroll
-    for (int i = 0; i < Q3; ++i) out[i * N + m] = upd ? f[i] : (inlet ? inlet3(p, i) : 0.0f);
+        for (int i = 0; i < Q3; ++i) f[i] = inlet ? p.ph.ein[i] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < Q3; ++i) out[i * N + m] = f[i];
 }
 
 template <int S, int L, class T>
@@ -1067,13 +1113,14 @@ __global__ void k3_macros(KParams3 p, const T* __restrict__ lat, float* __restri
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t N = p.g.nx * p.g.ny * p.g.nz;
     if (m >= N) return;
-    const int64_t x = m % p.g.nx, yz = m / p.g.nx, y = yz % p.g.ny, z = yz / p.g.ny;
-    const int64_t n = yz * p.g.px + x;
+    int64_t x, y, z;
+    split_index3(p.g, m, x, y, z);
+    const int64_t n = (z * p.g.ny + y) * p.g.px + x;
     const uint8_t t = p.types[n];
     float r = 0.0f, j[3] = {0.0f, 0.0f, 0.0f};
     if (updated(t)) {
         float f[Q3];
-        gather_state3<L, S>(p, lat, x, y, z, n, f);
+        gather_typed3<L, S>(p, lat, x, y, z, n, t, f);
         float rt;
         moments3(f, rt, j[0], j[1], j[2]);
         r = 1.0f + rt;
@@ -1119,11 +1166,13 @@ __global__ void __launch_bounds__(DIAG3_THREADS)
     double acc[DIAG3_VALUES] = {0, 0, 0, 0, 0, 0};
     for (int64_t m = (int64_t)blockIdx.x * DIAG3_THREADS + threadIdx.x; m < N;
          m += (int64_t)DIAG3_BLOCKS * DIAG3_THREADS) {
-        const int64_t x = m % p.g.nx, yz = m / p.g.nx, y = yz % p.g.ny, z = yz / p.g.ny;
-        const int64_t n = yz * p.g.px + x;
-        if (!updated(p.types[n])) continue;
+        int64_t x, y, z;
+        split_index3(p.g, m, x, y, z);
+        const int64_t n = (z * p.g.ny + y) * p.g.px + x;
+        const uint8_t t = p.types[n];
+        if (!updated(t)) continue;
         float f[Q3];
-        gather_state3<L, S>(p, lat, x, y, z, n, f);
+        gather_typed3<L, S>(p, lat, x, y, z, n, t, f);
         double r = 1.0, j[3] = {0.0, 0.0, 0.0};
 #pragma unroll
         for (int i = 0; i < Q3; ++i) {
