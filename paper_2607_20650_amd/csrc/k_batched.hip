@@ -1,15 +1,17 @@
 // k_batched.hip -- one launch advances every resident request of the serving
-// engine by one lattice update (two-lattice tiled pull, the same per-node code
-// as a single simulation, so a request's result does not depend on what else
-// is resident).
+// engine (two-lattice pull, the same per-node code as a single simulation, so a
+// request's result does not depend on what else is resident): by up to
+// BATCH_UPDATES lattice updates (k_batched_fused, marching strips), or by one
+// (k_batched, while a request is resident that needs single updates).
 //
 // The grid is persistent (fixed at graph capture): blocks walk a work list of
 // (slot, tile) items that the host rewrites between bundles, so one captured
 // graph serves any membership.  Launch k of a bundle advances a slot only
 // while k < its remaining updates, which stops every request at exactly its
-// requested step count.
+// requested step count.  Launch k of a bundle reads lattice k mod 2 of a
+// request and writes the other.
 //
-// Per work item the chain of dependent memory accesses is kept short: the
+// k_batched: per work item the chain of dependent memory accesses is kept short: the
 // 256-byte descriptor of the next item is fetched with one vector load (a
 // dword per lane) while the current item runs, and its fields are read from
 // the lanes; the work list is read two items ahead; the node type and the
@@ -23,17 +25,10 @@
 #include <cstddef>
 
 #include "lbm_batched.hpp"
-#include "lbm_device.hpp"
 #include "lbm_edges.hpp"
+#include "lbm_fused.hpp"
 
 namespace lbm {
-
-// The descriptor's pointers are generic (loaded from memory, not kernel
-// arguments); these views let the regular path use global-memory
-// instructions instead of flat ones.
-template <class T> using gptr = T __attribute__((address_space(1)))*;
-template <class T> __device__ __forceinline__ gptr<const T> as_global(const T* q) { return (gptr<const T>)q; }
-template <class T> __device__ __forceinline__ gptr<T> as_global(T* q) { return (gptr<T>)q; }
 
 // Field F of a descriptor held one dword per lane (dv), at byte offset OFF:
 // its dwords are read from their lanes (wavefront-uniform results).
@@ -80,8 +75,8 @@ __global__ void __launch_bounds__(256) k_batched(const SlotDesc* __restrict__ sl
         p.rout = rin2 ? rin2 + (parity ^ 1) * p.g.ny : nullptr;
         void* lat0 = from_lanes<void*, offsetof(SlotDesc, lat)>(mine);
         void* lat1 = from_lanes<void*, offsetof(SlotDesc, lat) + sizeof(void*)>(mine);
-        const T* src = (const T*)(parity ? lat1 : lat0);
-        T* dst = (T*)(parity ? lat0 : lat1);
+        const T* src = (const T*)((k & 1) ? lat1 : lat0);
+        T* dst = (T*)((k & 1) ? lat0 : lat1);
         const int x = it.x0 + (int)threadIdx.x;
         const int y = it.y0 + (int)threadIdx.y;
         if (x >= p.g.nx || y >= p.g.ny) continue;
@@ -117,26 +112,65 @@ __global__ void __launch_bounds__(256) k_batched(const SlotDesc* __restrict__ sl
     }
 }
 
-hipError_t launch_batched(int layout, int prec, const SlotDesc* slots, const WorkItem* work, const int32_t* n_work,
-                          int k, int blocks, hipStream_t s)
+// One work item per wavefront: a strip of BATCH_STRIP columns and `rows` rows
+// (n_work[1], chosen per bundle so that the items fill the chip).  The items of
+// a block are neighbours in the list.  On 16 requests of 0.02 - 0.33 M nodes a
+// bundle's launches took 22.3 us per update one at a time, bound by their
+// latency and by memory.
+template <int L, class T>
+__global__ void __launch_bounds__(256) k_batched_fused(const SlotDesc* __restrict__ slots,
+                                                       const WorkItem* __restrict__ work,
+                                                       const int32_t* __restrict__ n_work, int k)
+{
+    const int32_t nw = n_work[0], rows = n_work[1];
+    const uint32_t groups = (uint32_t)(nw + 3) / 4;
+    const int wave = (int)__builtin_amdgcn_readfirstlane(threadIdx.y);
+    for (uint32_t w = blockIdx.x; w < groups; w += gridDim.x) {
+        const int32_t item = (int32_t)xcd_tile(w, groups) * 4 + wave;
+        if (item >= nw) continue;
+        const WorkItem it = work[item];
+        const SlotDesc& d = slots[it.slot];
+        const int64_t left = d.steps_left - (int64_t)k * BATCH_UPDATES;
+        if (left <= 0) continue;
+        KParams p;
+        p.g = d.g;
+        p.ph = d.ph;
+        p.types = d.types;
+        p.links = d.links;
+        p.rin = nullptr;
+        p.rout = nullptr;
+        fused_strip<L, T, ST_PULL, BATCH_UPDATES, false>(
+            p, (const T*)d.lat[k & 1], (T*)d.lat[(k & 1) ^ 1], (int)min(left, (int64_t)BATCH_UPDATES), BATCH_UPDATES,
+            it.x0, it.y0, min(it.y0 + rows, (int)d.g.ny));
+    }
+}
+
+hipError_t launch_batched(int layout, int prec, bool fused, const SlotDesc* slots, const WorkItem* work,
+                          const int32_t* n_work, int k, int blocks, hipStream_t s)
 {
     const dim3 blk(BATCH_TILE_X, BATCH_TILE_Y);
     return with_layout_storage(layout, prec, [&](auto L, auto TT) {
-        hipLaunchKernelGGL((k_batched<decltype(L)::value, typename decltype(TT)::type>), dim3(blocks), blk, 0, s,
-                           slots, work, n_work, k);
+        constexpr int LV = decltype(L)::value;
+        using T = typename decltype(TT)::type;
+        if (fused)
+            hipLaunchKernelGGL((k_batched_fused<LV, T>), dim3(blocks), blk, 0, s, slots, work, n_work, k);
+        else
+            hipLaunchKernelGGL((k_batched<LV, T>), dim3(blocks), blk, 0, s, slots, work, n_work, k);
         return hipGetLastError();
     });
 }
 
-int batched_blocks(int layout, int prec)
+int batched_blocks(int layout, int prec, bool fused)
 {
     int dev = 0, cus = 0, per = 0;
     (void)hipGetDevice(&dev);
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
     const int threads = BATCH_TILE_X * BATCH_TILE_Y;
     const hipError_t e = with_layout_storage(layout, prec, [&](auto L, auto TT) {
-        return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per, k_batched<decltype(L)::value, typename decltype(TT)::type>, threads, 0);
+        constexpr int LV = decltype(L)::value;
+        using T = typename decltype(TT)::type;
+        return fused ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_batched_fused<LV, T>, threads, 0)
+                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_batched<LV, T>, threads, 0);
     });
     (void)hipGetLastError();
     if (e != hipSuccess || per <= 0) per = 4;

@@ -56,6 +56,9 @@ struct Request {
     int slot = -1;
     int64_t off = -1;
     int64_t steps_done = 0;
+    int cur = 0;         // the lattice that holds the state
+    bool single = false; // needs one update per launch
+    int32_t strips = 0;  // strips of BATCH_STRIP columns
     int64_t res_off = -1; // its readout in the pinned result arena (while in flight)
     int32_t status = LBM_OK;
     std::vector<float> rho, u;
@@ -119,14 +122,14 @@ struct lbm_server {
     std::unordered_map<uint64_t, Request*> reqs;
     std::vector<uint64_t> unreported;
     uint64_t next_id = 1;
-    // one captured bundle per persistent grid size: the full grid (resident
+    // captured bundles per persistent grid size: the full grid (resident
     // blocks on the device) and smaller ones down to 1/32 of it, so that a
-    // bundle over few work items launches few blocks
+    // bundle over few work items launches few blocks; [1]: several updates per
+    // launch, [0]: one (captured when a request that needs it is resident)
     static constexpr int NGRIDS = 6;
-    hipGraph_t graph[NGRIDS] = {};
-    hipGraphExec_t gexec[NGRIDS] = {};
-    int grid_blocks[NGRIDS] = {};
-    int blocks = 0;
+    hipGraph_t graph[2][NGRIDS] = {};
+    hipGraphExec_t gexec[2][NGRIDS] = {};
+    int grid_blocks[2][NGRIDS] = {};
     bool poisoned = false;
     std::string err;
     int64_t bundles = 0, node_updates = 0;
@@ -202,8 +205,8 @@ lbm_status enqueue_readout(lbm_server* s, Request* r)
 {
     const Geometry& g = r->kp.g;
     const int64_t N = g.nx * g.ny;
-    void* cur = lat_ptr(s->pool, r, (int)(r->steps & 1));
-    float* scratch = (float*)lat_ptr(s->pool, r, (int)((r->steps & 1) ^ 1)); // the other lattice
+    void* cur = lat_ptr(s->pool, r, r->cur);
+    float* scratch = (float*)lat_ptr(s->pool, r, r->cur ^ 1); // the other lattice
     KParams p = r->kp;
     if (r->rin2) p.rin = r->rin2 + (r->steps & 1) * g.ny;
     hipError_t e = launch_macros(ST_PULL, s->layout, s->precision, p, cur, scratch, scratch + N, s->stream);
@@ -335,6 +338,37 @@ lbm_status upload(lbm_server* s, Request* r, char* staged)
     return s->check(e, "request initialisation");
 }
 
+// Launches of a bundle of K updates.
+int bundle_launches(const lbm_server* s, bool fused)
+{
+    return fused ? (s->K + BATCH_UPDATES - 1) / BATCH_UPDATES : s->K;
+}
+
+// Capture the bundles of one kind, one per grid size: launch k advances every
+// slot that has updates left.
+bool capture_bundles(lbm_server* s, bool fused)
+{
+    const int blocks = batched_blocks(s->layout, s->precision, fused);
+    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
+        s->grid_blocks[fused][v] = std::max(1, blocks >> v);
+        if (s->gexec[fused][v]) continue;
+        if (hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
+        hipError_t e = hipSuccess;
+        for (int k = 0; k < bundle_launches(s, fused) && e == hipSuccess; ++k)
+            e = launch_batched(s->layout, s->precision, fused, s->d_slots, s->d_work, s->d_nwork, k,
+                               s->grid_blocks[fused][v], s->cap);
+        hipGraph_t g = nullptr;
+        const hipError_t e2 = hipStreamEndCapture(s->cap, &g);
+        if (e != hipSuccess || e2 != hipSuccess) {
+            if (g) (void)hipGraphDestroy(g);
+            return false;
+        }
+        s->graph[fused][v] = g;
+        if (hipGraphInstantiate(&s->gexec[fused][v], g, nullptr, nullptr, 0) != hipSuccess) return false;
+    }
+    return true;
+}
+
 } // namespace
 
 extern "C" {
@@ -365,7 +399,9 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
     s->slot_req.assign(max_slots, nullptr);
     // A full 64 x 4 tile needs >= 256 * (18 * elem + 1) bytes of pool; ragged
     // edge tiles are bounded per request.
-    s->work_cap = 2 * (s->budget / (256 * (18 * s->elem + 1))) + 1024 * (int64_t)max_slots + 1024;
+    // A strip of BATCH_STRIP x BATCH_MIN_ROWS nodes covers more nodes than a
+    // tile, but ragged edges can double a request's count.
+    s->work_cap = 4 * (s->budget / (256 * (18 * s->elem + 1))) + 2048 * (int64_t)max_slots + 2048;
 
     auto cleanup = [&](lbm_status st, const char* m) {
         lbm_server_destroy(s);
@@ -395,12 +431,12 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
     s->free_list[0] = s->budget;
     bool ok = hipMalloc((void**)&s->d_slots, sizeof(SlotDesc) * max_slots) == hipSuccess &&
               hipMalloc((void**)&s->d_work, sizeof(WorkItem) * s->work_cap) == hipSuccess &&
-              hipMalloc((void**)&s->d_nwork, sizeof(int32_t)) == hipSuccess;
+              hipMalloc((void**)&s->d_nwork, 2 * sizeof(int32_t)) == hipSuccess;
     for (int k = 0; k < 2 && ok; ++k)
         ok = hipHostMalloc((void**)&s->h_slots[k], sizeof(SlotDesc) * max_slots, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&s->h_work[k], sizeof(WorkItem) * s->work_cap, hipHostMallocDefault) ==
                  hipSuccess &&
-             hipHostMalloc((void**)&s->h_nwork[k], sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
+             hipHostMalloc((void**)&s->h_nwork[k], 2 * sizeof(int32_t), hipHostMallocDefault) == hipSuccess;
     // result arena: grows on demand (only while nothing is in flight)
     s->res_cap = std::min<int64_t>(s->budget, (int64_t)64 << 20);
     ok = ok && hipHostMalloc((void**)&s->h_res, (size_t)s->res_cap, hipHostMallocDefault) == hipSuccess;
@@ -410,31 +446,12 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
     }
     for (int k = 0; k < 2; ++k) {
         std::memset(s->h_slots[k], 0, sizeof(SlotDesc) * max_slots);
-        *s->h_nwork[k] = 0;
+        s->h_nwork[k][0] = s->h_nwork[k][1] = 0;
     }
     if (hipMemcpy(s->d_slots, s->h_slots[0], sizeof(SlotDesc) * max_slots, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(s->d_nwork, s->h_nwork[0], sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
+        hipMemcpy(s->d_nwork, s->h_nwork[0], 2 * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
         return cleanup(LBM_EDEVICE, "descriptor upload failed");
-    s->blocks = batched_blocks(layout, precision);
-
-    // the bundle: K launches, launch k advancing every slot with k < steps_left
-    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
-        s->grid_blocks[v] = std::max(1, s->blocks >> v);
-        if (hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal) != hipSuccess)
-            return cleanup(LBM_EDEVICE, "hipStreamBeginCapture failed");
-        hipError_t e = hipSuccess;
-        for (int k = 0; k < s->K && e == hipSuccess; ++k)
-            e = launch_batched(layout, precision, s->d_slots, s->d_work, s->d_nwork, k, s->grid_blocks[v], s->cap);
-        hipGraph_t g = nullptr;
-        hipError_t e2 = hipStreamEndCapture(s->cap, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return cleanup(LBM_EDEVICE, "bundle capture failed");
-        }
-        s->graph[v] = g;
-        if (hipGraphInstantiate(&s->gexec[v], g, nullptr, nullptr, 0) != hipSuccess)
-            return cleanup(LBM_EDEVICE, "bundle instantiation failed");
-    }
+    if (!capture_bundles(s, true)) return cleanup(LBM_EDEVICE, "bundle capture failed");
     *out = s;
     return LBM_OK;
 }
@@ -471,7 +488,14 @@ lbm_status lbm_server_submit(lbm_server* s, const lbm_grid* grid, const uint8_t*
                    align_up(g.px * g.ny * (int64_t)sizeof(uint32_t));
     if (bc->x_axis == LBM_NEUMANN_OUTFLOW || bc->x_axis == LBM_NEUMANN_PRESSURE)
         r->footprint += align_up(2 * g.ny * (int64_t)sizeof(float));
-    r->tiles = g.ntx * g.nty;
+    r->strips = (int32_t)((g.nx + BATCH_STRIP - 1) / BATCH_STRIP);
+    const int64_t strip_items = r->strips * ((g.ny + BATCH_MIN_ROWS - 1) / BATCH_MIN_ROWS);
+    // the Neumann inlet, rows too long for 31-bit byte offsets and periodic
+    // heights below the updates per launch take one update per launch
+    const int64_t row_bytes = g.px * s->elem * (s->layout == L_STREAM ? 1 : (s->layout == L_BUNDLE ? 3 : 9));
+    r->single = bc->x_axis == LBM_NEUMANN_OUTFLOW || bc->x_axis == LBM_NEUMANN_PRESSURE ||
+                row_bytes >= ((int64_t)1 << 30) || (g.ya == AX_PERIODIC && g.ny < BATCH_UPDATES);
+    r->tiles = (int32_t)std::max<int64_t>((int64_t)g.ntx * g.nty, strip_items);
     if (r->footprint > s->budget || r->tiles > s->work_cap) {
         delete r;
         return s->fail(LBM_ENOMEM, "request footprint exceeds the server's HBM budget");
@@ -536,6 +560,17 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
     int32_t nw = 0;
     InFlight b;
     int64_t res_bytes = 0;
+    // several updates per launch unless a resident request needs single ones;
+    // strips of as many rows as make about 2560 items (2.5 wavefronts per
+    // SIMD): fewer rows cost recomputed ones, more leave the chip idle
+    bool fused = true;
+    int64_t strip_rows = 0;
+    for (const Request* r : s->slot_req)
+        if (r) {
+            fused = fused && !r->single;
+            strip_rows += r->strips * r->kp.g.ny;
+        }
+    const int32_t rows = (int32_t)std::min<int64_t>(std::max<int64_t>(strip_rows / 2560, BATCH_MIN_ROWS), 64);
     for (int k = 0; k < s->max_slots; ++k) {
         Request* r = s->slot_req[k];
         SlotDesc& d = hs[k];
@@ -544,20 +579,25 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
             continue;
         }
         const Geometry& g = r->kp.g;
-        d.lat[0] = lat_ptr(s->pool, r, 0);
-        d.lat[1] = lat_ptr(s->pool, r, 1);
+        d.lat[0] = lat_ptr(s->pool, r, r->cur);
+        d.lat[1] = lat_ptr(s->pool, r, r->cur ^ 1);
         d.types = r->kp.types;
         d.links = r->kp.links;
         d.rin2 = r->rin2;
         d.g = g;
         d.ph = r->kp.ph;
         d.steps_done = r->steps_done;
-        d.steps_left = r->steps - r->steps_done;
-        for (int32_t ty = 0; ty < g.nty; ++ty)
-            for (int32_t tx = 0; tx < g.ntx; ++tx) hw[nw++] = WorkItem{k, tx * g.tx, ty * g.ty};
-        const int64_t adv = std::min<int64_t>(s->K, d.steps_left);
+        const int64_t adv = std::min<int64_t>(s->K, r->steps - r->steps_done);
+        d.steps_left = adv;
+        if (fused) {
+            for (int32_t y = 0; y < (int32_t)g.ny; y += rows)
+                for (int32_t c = 0; c < r->strips; ++c) hw[nw++] = WorkItem{k, c * BATCH_STRIP, y};
+        } else {
+            for (int32_t ty = 0; ty < g.nty; ++ty)
+                for (int32_t tx = 0; tx < g.ntx; ++tx) hw[nw++] = WorkItem{k, tx * g.tx, ty * g.ty};
+        }
         b.updates += adv * g.nx * g.ny;
-        if (adv == d.steps_left) {
+        if (adv == r->steps - r->steps_done) {
             r->res_off = res_bytes; // relative to the bundle's region for now
             res_bytes += 3 * g.nx * g.ny * (int64_t)sizeof(float);
             b.finishing.push_back(r);
@@ -598,20 +638,29 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
             o += (r->kp.g.nx * r->kp.g.ny + 15) / 16 * 16;
         }
     }
-    *s->h_nwork[s->stage] = nw;
+    if (!fused && !s->gexec[0][lbm_server::NGRIDS - 1] && !capture_bundles(s, false))
+        return s->fail(LBM_EDEVICE, "bundle capture failed");
+    s->h_nwork[s->stage][0] = nw;
+    s->h_nwork[s->stage][1] = rows;
     hipError_t e = hipMemcpyAsync(s->d_slots, hs, sizeof(SlotDesc) * s->max_slots, hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(s->d_work, hw, sizeof(WorkItem) * nw, hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(s->d_nwork, s->h_nwork[s->stage], sizeof(int32_t), hipMemcpyHostToDevice, s->stream);
-    // the smallest captured grid with at least one block per work item
+        e = hipMemcpyAsync(s->d_nwork, s->h_nwork[s->stage], 2 * sizeof(int32_t), hipMemcpyHostToDevice, s->stream);
+    // the smallest captured grid with at least one block per work item (four
+    // strips)
+    const int32_t need = fused ? (nw + 3) / 4 : nw;
     int v = 0;
-    while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[v + 1] >= nw) ++v;
-    if (e == hipSuccess) e = hipGraphLaunch(s->gexec[v], s->stream);
+    while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[fused][v + 1] >= need) ++v;
+    if (e == hipSuccess) e = hipGraphLaunch(s->gexec[fused][v], s->stream);
     st = s->check(e, "bundle launch");
     if (st != LBM_OK) return st;
     for (Request* r : s->slot_req)
-        if (r) r->steps_done += std::min<int64_t>(s->K, r->steps - r->steps_done);
+        if (r) {
+            const int64_t adv = std::min<int64_t>(s->K, r->steps - r->steps_done);
+            r->cur ^= (int)(((fused ? (adv + BATCH_UPDATES - 1) / BATCH_UPDATES : adv)) & 1);
+            r->steps_done += adv;
+        }
     for (Request* r : b.finishing) {
         r->res_off += roff + up_bytes;
         st = enqueue_readout(s, r);
@@ -691,10 +740,11 @@ void lbm_server_destroy(lbm_server* s)
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (auto& kv : s->reqs) delete kv.second;
     s->reqs.clear();
-    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
-        if (s->gexec[v]) (void)hipGraphExecDestroy(s->gexec[v]);
-        if (s->graph[v]) (void)hipGraphDestroy(s->graph[v]);
-    }
+    for (int f = 0; f < 2; ++f)
+        for (int v = 0; v < lbm_server::NGRIDS; ++v) {
+            if (s->gexec[f][v]) (void)hipGraphExecDestroy(s->gexec[f][v]);
+            if (s->graph[f][v]) (void)hipGraphDestroy(s->graph[f][v]);
+        }
     for (InFlight& b : s->flight) s->free_events.push_back(b.ev);
     s->flight.clear();
     for (hipEvent_t ev : s->free_events) (void)hipEventDestroy(ev);
