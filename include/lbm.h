@@ -224,14 +224,17 @@ typedef struct {
     int32_t tile_x, tile_y;  /* tile chosen for tiled schemes (0 for LPTL) */
     int32_t block;           /* threads per block of the update kernel */
     int32_t bundle;          /* updates per cached HIP graph (0 = no graphs) */
-    int64_t device_bytes;    /* device memory owned by the context */
+    int64_t device_bytes;    /* device memory owned by the context (a one-lattice scheme holds a second
+                                lattice, for launches of several updates, while one takes at most 1 GiB) */
     int64_t fluid_nodes;     /* fluid + outlet nodes */
 } lbm_info;
 
 lbm_status lbm_get_info(const lbm_ctx* ctx, lbm_info* info);
 
-/* lbm_set_bundle -- updates per cached HIP graph used by lbm_step (0 = launch
- * each update directly).  Default 32. */
+/* lbm_set_bundle -- updates per cached HIP graph used by lbm_step; a launch does
+ * as many of them as suit the grid (the result is bitwise that of single
+ * updates).  0 = one launch of the scheme's own kernel per update, no graph.
+ * Default 32. */
 lbm_status lbm_set_bundle(lbm_ctx* ctx, int32_t k);
 
 /* lbm_sync -- wait for all work enqueued on the context's stream. */
@@ -267,9 +270,9 @@ int32_t lbm_bytes_per_update(int32_t precision);
  * slot and space in the HBM budget are free (arrival order, later requests
  * may pass one that does not fit yet), kept resident, and advanced together:
  * every bundle is one replay of a captured HIP graph of `bundle_steps`
- * launches of a persistent batched kernel, each launch one lattice update of
- * every resident request (two-lattice tiled pull, same arithmetic as
- * lbm_step, so a request's result is independent of the mix).  A request
+ * updates of every resident request by a persistent batched kernel, up to four
+ * updates per launch (two-lattice pull, same arithmetic as lbm_step, so a
+ * request's result is independent of the mix).  A request
  * stops at exactly its step count; its rho and u are then read back and its
  * memory freed.
  * ---------------------------------------------------------------------- */

@@ -42,6 +42,14 @@ bool is_inout(int axis) { return axis >= LBM_INFLOW_OUTFLOW && axis <= LBM_NEUMA
 bool is_pressure_outlet(int axis) { return axis == LBM_INFLOW_PRESSURE || axis == LBM_NEUMANN_PRESSURE; }
 bool is_neumann_inlet(int axis) { return axis == LBM_NEUMANN_OUTFLOW || axis == LBM_NEUMANN_PRESSURE; }
 
+// Largest lattice that a one-lattice scheme gets a second one beside, for
+// launches of several updates (a block may not overwrite what its neighbours
+// still read).  Per update, three simulations in turn: AA 4096 x 1024 FP32 53
+// us in place, 21 us between two lattices; NPOL 3001 x 1499 FP32 bundle 69 and
+// 20 us.  1 GiB is 1/288 of the device; larger grids, where one lattice is
+// what the scheme is chosen for, keep to single updates in place.
+constexpr size_t SPARE_MOST = (size_t)1 << 30;
+
 // One-lattice schemes that exchange through the tile buffer grid.
 bool has_buffer_grid(int scheme) { return scheme == S_NPOL || scheme == S_NSOL; }
 
@@ -78,13 +86,14 @@ struct lbm_ctx {
     double* dout = nullptr;
     int64_t lat_elems = 0, edge_elems = 0;
     int64_t t = 0;
-    int cur = 0;    // two-lattice schemes: the lattice that holds the state
+    int cur = 0;    // the lattice that holds the state
+    bool edges_old = false; // one-lattice tiled schemes: edge[] is not that of the state
     FusedPlan plan; // several updates per launch
     int32_t bundle = 32;
     int32_t block = 256;
-    hipGraph_t graph[2] = {nullptr, nullptr};
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    int graph_cur[2] = {0, 0}; // the lattice that holds the state after each graph
+    hipGraph_t graph[4] = {}; // by graph_key
+    hipGraphExec_t gexec[4] = {};
+    int graph_cur[4] = {}; // the lattice that holds the state after each graph
     bool have_prev = false;
     bool poisoned = false;
     std::string err;
@@ -123,13 +132,20 @@ struct lbm_ctx {
 
 namespace {
 
-void free_all(lbm_ctx* c)
+void drop_graphs(lbm_ctx* c)
 {
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < 4; ++k) {
         if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
         if (c->graph[k]) (void)hipGraphDestroy(c->graph[k]);
         c->gexec[k] = nullptr;
         c->graph[k] = nullptr;
+    }
+}
+
+void free_all(lbm_ctx* c)
+{
+    drop_graphs(c);
+    for (int k = 0; k < 2; ++k) {
         if (c->lat_raw[k]) (void)hipFree(c->lat_raw[k]);
         if (c->edge[k]) (void)hipFree(c->edge[k]);
         c->lat[k] = c->lat_raw[k] = c->edge[k] = nullptr;
@@ -262,42 +278,49 @@ lbm_status launch_one(lbm_ctx* c, int parity, int cur, hipStream_t s)
     const KParams p = c->at(parity, true);
     hipError_t e;
     if (c->grid.scheme == S_AA)
-        e = launch_aa(c->grid.layout, c->grid.precision, p, parity, c->lat[0], c->obuf, s);
+        e = launch_aa(c->grid.layout, c->grid.precision, p, parity, c->lat[cur], c->obuf, s);
     else if (is_two_lattice(c->grid.scheme))
         e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, c->lat[cur],
                           c->lat[cur ^ 1], nullptr, nullptr, s);
     else
-        e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, nullptr, c->lat[0],
+        e = launch_update(c->grid.scheme, c->grid.layout, c->grid.precision, p, c->block, nullptr, c->lat[cur],
                           c->edge[parity], c->edge[parity ^ 1], s);
     return c->check(e, "update launch");
 }
 
 // n updates on stream s from update count t on, the state in lattice cur
 // (cur moves along): in as few launches as `most` updates per launch allow,
-// evenly filled.
+// evenly filled.  AA's two kinds of update make pairs: an odd count starts or
+// ends with a single one.
 lbm_status launch_updates(lbm_ctx* c, int64_t t, int64_t n, int most, int& cur, hipStream_t s)
 {
+    const int unit = c->grid.scheme == S_AA ? 2 : 1;
     const bool two = is_two_lattice(c->grid.scheme);
     for (int64_t left = n; left > 0;) {
-        const int64_t launches = (left + most - 1) / most;
-        const int kk = (int)((left + launches - 1) / launches);
-        lbm_status st;
-        if (kk == 1)
-            st = launch_one(c, (int)((t + n - left) & 1), cur, s);
-        else
-            st = c->check(launch_fused(c->grid.scheme, c->grid.layout, c->grid.precision, c->kp, c->plan, kk,
-                                       c->lat[cur], c->lat[cur ^ 1], s),
-                          "update launch");
+        const int64_t now = t + n - left;
+        int kk = 1;
+        if (most > 1 && now % unit == 0 && left >= unit) {
+            const int64_t units = left / unit, launches = (units * unit + most - 1) / most;
+            kk = (int)((units + launches - 1) / launches) * unit;
+        }
+        // the edge buffers are not kept up to date between fused launches
+        const bool fused = kk > 1 || (most > 1 && has_buffer_grid(c->grid.scheme));
+        const lbm_status st =
+            fused ? c->check(launch_fused(c->grid.scheme, c->grid.layout, c->grid.precision, c->kp, c->plan, kk,
+                                          c->lat[cur], c->lat[cur ^ 1], s),
+                             "update launch")
+                  : launch_one(c, (int)(now & 1), cur, s);
         if (st != LBM_OK) return st;
-        if (two) cur ^= 1;
+        if (two || fused) cur ^= 1;
         left -= kk;
     }
     return LBM_OK;
 }
 
-// Which cached graph serves the next bundle: a graph holds the lattices it
-// was captured with (two-lattice schemes) or starts at one update parity.
-int graph_key(const lbm_ctx* c) { return is_two_lattice(c->grid.scheme) ? c->cur : (int)(c->t & 1); }
+// Which cached graph serves the next bundle: a graph holds the lattices it was
+// captured with and, with one lattice or a Neumann inlet, starts at one update
+// parity (elsewhere the parity follows the lattice or does not matter).
+int graph_key(const lbm_ctx* c) { return c->cur * 2 + (is_two_lattice(c->grid.scheme) ? 0 : (int)(c->t & 1)); }
 
 lbm_status build_graph(lbm_ctx* c, int key)
 {
@@ -322,16 +345,6 @@ lbm_status build_graph(lbm_ctx* c, int key)
     c->gexec[key] = x;
     c->graph_cur[key] = cur;
     return LBM_OK;
-}
-
-void drop_graphs(lbm_ctx* c)
-{
-    for (int k = 0; k < 2; ++k) {
-        if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
-        if (c->graph[k]) (void)hipGraphDestroy(c->graph[k]);
-        c->gexec[k] = nullptr;
-        c->graph[k] = nullptr;
-    }
 }
 
 lbm_status ensure_readout(lbm_ctx* c)
@@ -545,6 +558,10 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     const size_t raw_bytes = lat_bytes + 2 * (size_t)c->guard * c->elem;
     lbm_status st = alloc(c, &c->lat_raw[0], raw_bytes);
     if (st == LBM_OK && is_two_lattice(grid->scheme)) st = alloc(c, &c->lat_raw[1], raw_bytes);
+    if (st == LBM_OK && !is_two_lattice(grid->scheme) && raw_bytes <= SPARE_MOST && !is_neumann_inlet(bc->x_axis)) {
+        c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
+        if (c->plan.kk > 1 && alloc(c, &c->lat_raw[1], raw_bytes) != LBM_OK) c->plan = FusedPlan{};
+    }
     for (int k = 0; k < 2; ++k)
         if (c->lat_raw[k]) c->lat[k] = (char*)c->lat_raw[k] + (size_t)c->guard * c->elem;
     if (st == LBM_OK && c->edge_elems) st = alloc(c, &c->edge[0], (size_t)c->edge_elems * c->elem);
@@ -588,7 +605,8 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     }
     c->block = grid->scheme == LBM_LPTL ? lptl_block_size(grid->layout, grid->precision)
                                         : (g.tx / g.vx) * g.ty;
-    if (!c->rin) c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
+    if (is_two_lattice(grid->scheme) && !c->rin)
+        c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
     *out = c;
     return LBM_OK;
 }
@@ -598,6 +616,14 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
+    const int most = c->bundle > 0 ? c->plan.kk : 1;
+    if (n > 0 && c->edge_elems && most > 1) c->edges_old = true;
+    if (n > 0 && c->edges_old && most == 1) {
+        const hipError_t e = launch_edge_fill(c->state, c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
+                                              c->edge[c->t & 1], c->stream);
+        if (e != hipSuccess) return c->check(e, "edge fill");
+        c->edges_old = false;
+    }
     while (c->bundle > 0 && n >= c->bundle) {
         const int key = graph_key(c);
         if (!c->gexec[key]) {
@@ -611,7 +637,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
         n -= c->bundle;
     }
     if (n > 0) {
-        lbm_status st = launch_updates(c, c->t, n, c->bundle > 0 ? c->plan.kk : 1, c->cur, c->stream);
+        lbm_status st = launch_updates(c, c->t, n, most, c->cur, c->stream);
         if (st != LBM_OK) return st;
         c->t += n;
     }
@@ -705,6 +731,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     if (e == hipSuccess && c->edge_elems)
         e = launch_edge_fill(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                              c->edge[c->t & 1], c->stream);
+    c->edges_old = false;
     if (e == hipSuccess && c->obuf && c->state_now() == ST_SWAP)
         e = launch_aa_outlet_fill(c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), c->obuf, c->stream);
     if (borrow) {

@@ -1,5 +1,7 @@
-// k_fused.hip -- several lattice updates per launch for the two-lattice
-// schemes (LPTL, NPTL, PUSH), every layout and storage precision.
+// k_fused.hip -- several lattice updates per launch, every scheme, layout and
+// storage precision: from one lattice to another, in the state kind the scheme
+// keeps (the one-lattice schemes have a second lattice on grids up to 1 GiB;
+// AA comes here at even update counts, in its push state).
 //
 // One update per launch is bound by memory: 18 stored values move per node and
 // update, about 75 FP32 instructions run on them.  Here a wavefront takes a
@@ -53,7 +55,7 @@ constexpr int FUSED_WAVES = 4;
 } // namespace
 
 template <int L, class T, int S>
-__global__ void __launch_bounds__(64 * FUSED_WAVES, S == ST_PULL || sizeof(T) == 2 ? 4 : 3)
+__global__ void __launch_bounds__(64 * FUSED_WAVES, S != ST_PUSH || sizeof(T) == 2 ? 4 : 3)
     k_fused(KParams p, const T* __restrict__ src, T* __restrict__ dst, int kk, int rows, int strip_blocks)
 {
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x);
@@ -118,7 +120,7 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
     const float ein[3] = {inlet_value(p, 2), inlet_value(p, 5), inlet_value(p, 8)};
     float f[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) f[i] = e.get(i);
+    for (int i = 0; i < 9; ++i) f[i] = e.get(slot<S>(i));
     auto fix_outlet = [&]() {
         if (fix) {
             keep_branch();
@@ -188,7 +190,7 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
         }
     }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) e.put(i, st<T>(f[i]));
+    for (int i = 0; i < 9; ++i) e.put(slot<S>(i), st<T>(f[i]));
     if (lk & LINK_NONE) { // nodes that are not updated hold 0
 #pragma unroll
         for (int i = 0; i < 9; ++i) e.v[i] = 0u;
@@ -204,8 +206,7 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     const int64_t stride = layout == L_STREAM ? 1 : (layout == L_BUNDLE ? 3 : 9);
     // the Neumann inlet and full-way bounce-back keep the single-update
     // kernels; byte offsets within a row stay below OFF_NONE
-    if ((scheme != S_LPTL && scheme != S_NPTL && scheme != S_PUSH) || g.fw || p.rin != nullptr ||
-        g.px * stride * elem >= ((int64_t)1 << 30))
+    if (g.fw || p.rin != nullptr || g.px * stride * elem >= ((int64_t)1 << 30))
         return q;
     auto tiles = [&](int kk) {
         const int w = 64 - 2 * kk, h = TILE_ROWS - 2 * kk;
@@ -220,9 +221,10 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // with other simulations beside it).
     if (g.nx * g.ny <= 700000) {
         q.tile = 1;
-        q.kk = 3;
-        for (int kk : {7, 5, 4})
-            if (q.kk == 3 && tiles(kk) <= 256) q.kk = kk;
+        const int unit = scheme == S_AA ? 2 : 1; // AA's updates come in pairs
+        q.kk = 7 / unit * unit;
+        while (q.kk > 4 && tiles(q.kk) > 256) q.kk -= unit;
+        if (unit == 1 && tiles(q.kk) > 256) q.kk = 3;
         return q;
     }
     // FP16C on lattices that fit the 256 MB cache is bound by its codec either
@@ -234,6 +236,8 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // (4096 x 1024 FP32: 21.4 us per update; 768 blocks 23.0, 512 27.2, 1280
     // 24.1); at most 128 rows.
     q.kk = (int)std::min<int64_t>(prec == P_FP32 ? fused_most<float>() : fused_most<uint16_t>(), g.ny);
+    if (scheme == S_AA) q.kk &= ~1;
+    if (q.kk < 2) return FusedPlan{};
     const int64_t w = (int64_t)(64 - 2 * q.kk) * FUSED_WAVES, cols = (g.nx + w - 1) / w;
     const int64_t chunks = std::max<int64_t>(1024 / cols, 1);
     const int64_t rows = (g.ny + chunks - 1) / chunks;
@@ -263,7 +267,8 @@ hipError_t launch_fused(int scheme, int layout, int prec, const KParams& p, cons
                                    (const T*)src, (T*)dst, kk, rows, (int)cols);
             return hipGetLastError();
         };
-        return scheme == S_PUSH ? go(IC<ST_PUSH>{}) : go(IC<ST_PULL>{});
+        if (scheme == S_NSOL) return go(IC<ST_SWAP>{});
+        return scheme == S_PUSH || scheme == S_AA ? go(IC<ST_PUSH>{}) : go(IC<ST_PULL>{});
     });
 }
 

@@ -141,6 +141,9 @@ template <int I> __device__ __forceinline__ void by_side(uint32_t lk, float& f, 
 // compiler runs the selects on every row.
 __device__ __forceinline__ void keep_branch() { asm volatile(""); }
 
+// The slot that holds direction i in state kind S.
+template <int S> __device__ constexpr int slot(int i) { return S == ST_SWAP ? dir_opp(i) : i; }
+
 // What an update keeps between rows: the started inflow (directions 3..8) of
 // the last row it was given and that row's c_y = +1 results.
 struct Carry {
@@ -199,7 +202,8 @@ __device__ __forceinline__ void stream_row(const float* ein, bool inout, const f
 
 // kk updates of the nodes in columns x0 .. x0 + 63 - 2 halo of rows y0 .. y1 - 1
 // by the calling wavefront, src -> dst.  S: ST_PULL (stored values are
-// post-collision results) or ST_PUSH (streamed values).  1 <= kk <= K, kk <=
+// post-collision results), ST_SWAP (the same, each in the opposite direction's
+// slot) or ST_PUSH (streamed values).  1 <= kk <= K, kk <=
 // halo and, on a periodic y axis, kk <= ny.  STEP: a block barrier after every
 // row (every wavefront of the block walks the same rows).
 template <int L, class T, int S, int K, bool STEP>
@@ -265,7 +269,7 @@ __device__ __forceinline__ void fused_strip(const KParams& p, const T* src, T* d
         // row y is here; row y + 1 is sent for
         float f[9];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) f[i] = nv.get(i);
+        for (int i = 0; i < 9; ++i) f[i] = nv.get(slot<S>(i));
 #pragma unroll
         for (int l = K; l > 0; --l) lk[l] = lk[l - 1];
         lk[0] = nlk;
@@ -319,7 +323,7 @@ __device__ __forceinline__ void fused_strip(const KParams& p, const T* src, T* d
         }
         R e;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) e.put(i, st<T>(f[i]));
+        for (int i = 0; i < 9; ++i) e.put(slot<S>(i), st<T>(f[i]));
         const int yo = y - kk;
         if ((any >> kk) & 1u) { // nodes that are not updated hold 0
             keep_branch();

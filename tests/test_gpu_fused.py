@@ -58,3 +58,34 @@ def test_large_grids_bitwise(nx, ny, precision):
 def test_large_grid_layouts_bitwise():
     _compare(1011, 707, AXES[2:4], ["LPTL", "NPTL", "PUSH"], ["bundle", "collision"], ["fp32", "fp16sr", "fp16c"],
              calls=(8, 5))
+
+
+@pytest.mark.parametrize("precision", ALL_PRECISIONS)
+@pytest.mark.parametrize("nx,ny", [(128, 64), (37, 20), (5, 3), (57, 5), (200, 101), (1009, 701), (90001, 8), (13, 60001)])
+def test_one_lattice_schemes_bitwise(nx, ny, precision):
+    """AA in pairs of updates, NPOL and NSOL without their edge buffers, from
+    odd and even update counts, and back to single updates in between."""
+    from paper_2607_20650_amd.lbm import Simulation
+    small = nx * ny < 100000
+    for xa, ya in AXES if small else AXES[1:3]:
+        flags = W.random_flags(nx, ny, 0.1, nx + ny)
+        st = W.random_state(nx, ny, 0.02, 3, dtype=np.float32)
+        for scheme in ["AA", "NPOL", "NSOL"]:
+            for layout in ALL_LAYOUTS if small else ["stream"]:
+                out = []
+                for bundle in (0, 16):
+                    kw = dict(scheme=scheme, layout=layout, precision=precision)
+                    with Simulation(flags, 0.8, xa, ya, u_in=(0.05, 0.01), g=(1e-4, 2e-4), u0=(0.02, 0.0),
+                                    bundle=bundle, **kw) as sim:
+                        sim.step(5)
+                        sim.step(19)
+                        a = sim.populations()
+                        sim.set_state(st)
+                        sim.step(8)
+                        sim._check(sim._lib.lbm_set_bundle(sim._ctx, 0))
+                        sim.step(3)
+                        sim._check(sim._lib.lbm_set_bundle(sim._ctx, bundle))
+                        sim.step(6)
+                        out.append((a, sim.populations()))
+                for a, b in zip(*out):
+                    assert np.array_equal(a, b, equal_nan=True), (nx, ny, xa, ya, kw, np.argwhere(a != b)[:3])
