@@ -225,7 +225,7 @@ typedef struct {
     int32_t block;           /* threads per block of the update kernel */
     int32_t bundle;          /* updates per cached HIP graph (0 = no graphs) */
     int64_t device_bytes;    /* device memory owned by the context (a one-lattice scheme holds a second
-                                lattice, for launches of several updates, while one takes at most 1 GiB) */
+                                lattice, for launches of several updates, while one takes at most 1.5 GiB) */
     int64_t fluid_nodes;     /* fluid + outlet nodes */
 } lbm_info;
 

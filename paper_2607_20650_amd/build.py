@@ -19,7 +19,8 @@ LIB = os.path.join(PKG, "liblbm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["k_update.hip", "k_fused.hip", "k_aux.hip", "k_batched.hip", "context.hip", "server.hip", "k_d3q19.hip", "context3.hip"]
+SOURCES = ["k_update.hip", "k_fused.hip", "k_aux.hip", "k_batched.hip", "context.hip", "server.hip", "k_d3q19.hip", "k_d3q19_fused.hip",
+           "context3.hip"]
 
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",

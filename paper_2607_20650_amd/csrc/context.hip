@@ -42,14 +42,6 @@ bool is_inout(int axis) { return axis >= LBM_INFLOW_OUTFLOW && axis <= LBM_NEUMA
 bool is_pressure_outlet(int axis) { return axis == LBM_INFLOW_PRESSURE || axis == LBM_NEUMANN_PRESSURE; }
 bool is_neumann_inlet(int axis) { return axis == LBM_NEUMANN_OUTFLOW || axis == LBM_NEUMANN_PRESSURE; }
 
-// Largest lattice that a one-lattice scheme gets a second one beside, for
-// launches of several updates (a block may not overwrite what its neighbours
-// still read).  Per update, three simulations in turn: AA 4096 x 1024 FP32 53
-// us in place, 21 us between two lattices; NPOL 3001 x 1499 FP32 bundle 69 and
-// 20 us.  1 GiB is 1/288 of the device; larger grids, where one lattice is
-// what the scheme is chosen for, keep to single updates in place.
-constexpr size_t SPARE_MOST = (size_t)1 << 30;
-
 // One-lattice schemes that exchange through the tile buffer grid.
 bool has_buffer_grid(int scheme) { return scheme == S_NPOL || scheme == S_NSOL; }
 

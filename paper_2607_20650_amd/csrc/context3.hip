@@ -9,6 +9,7 @@
 #include "lbm.h"
 #include "lbm3.hpp"
 #include "lbm3_kernels.hpp"
+#include "lbm_host.hpp"
 
 using namespace lbm;
 
@@ -41,6 +42,7 @@ struct lbm3_ctx {
     void* lat[2] = {nullptr, nullptr};
     void* obuf = nullptr; // AA with an outlet: 5 values per (y, z) row
     uint8_t* types = nullptr;
+    uint32_t* links = nullptr; // link words, where launches do several updates
     float* readout = nullptr; // 19 * N floats, lazily
     double* u_prev = nullptr; // 3 * padded nodes, lazily (diagnostics)
     double* partials = nullptr;
@@ -48,6 +50,7 @@ struct lbm3_ctx {
     bool have_prev = false;
     int64_t lat_elems = 0;
     int64_t t = 0;
+    int now = 0; // the lattice that holds the state
     bool poisoned = false;
     std::string err;
 
@@ -65,7 +68,7 @@ struct lbm3_ctx {
     bool aa() const { return grid.scheme == LBM_AA; }
     // AA holds the push form at even update counts, the swap form at odd ones
     int state() const { return aa() ? ((t & 1) ? ST_SWAP : ST_PUSH) : ST_PULL; }
-    void* cur() const { return aa() ? lat[0] : lat[t & 1]; }
+    void* cur() const { return lat[now]; }
     int64_t nodes() const { return grid.nx * grid.ny * grid.nz; }
 };
 
@@ -73,13 +76,14 @@ namespace {
 
 void free3(lbm3_ctx* c)
 {
-    for (void* p : {c->lat[0], c->lat[1], c->obuf, (void*)c->types, (void*)c->readout, (void*)c->u_prev,
+    for (void* p : {c->lat[0], c->lat[1], c->obuf, (void*)c->types, (void*)c->links, (void*)c->readout, (void*)c->u_prev,
                     (void*)c->partials, (void*)c->dout})
         if (p) (void)hipFree(p);
     c->u_prev = nullptr;
     c->partials = c->dout = nullptr;
     c->lat[0] = c->lat[1] = c->obuf = nullptr;
     c->types = nullptr;
+    c->links = nullptr;
     c->readout = nullptr;
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     c->stream = nullptr;
@@ -222,8 +226,23 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
         return create3_error(LBM_ENOMEM, "device memory exhausted");
     }
     c->kp.types = c->types;
+    // several updates per launch need link words and, for AA, a second lattice;
+    // without memory for them every update is a launch of its own
+    if (fused3_serves(g, grid->layout, grid->precision) && (grid->scheme != LBM_AA || lat_bytes <= SPARE_MOST)) {
+        bool extra = hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) == hipSuccess;
+        if (!extra) c->links = nullptr;
+        if (extra && grid->scheme == LBM_AA && hipMalloc(&c->lat[1], lat_bytes) != hipSuccess) {
+            c->lat[1] = nullptr;
+            (void)hipFree(c->links);
+            c->links = nullptr;
+            extra = false;
+        }
+        if (!extra) (void)hipGetLastError();
+    }
+    c->kp.links = c->links;
     hipError_t e = hipMemcpyAsync(dflags, flags, (size_t)N, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = launch3_types(g, dflags, c->types, c->stream);
+    if (e == hipSuccess && c->links) e = launch3_links(g, c->types, c->links, c->stream);
     for (int k = 0; k < 2; ++k)
         if (e == hipSuccess && c->lat[k]) e = hipMemsetAsync(c->lat[k], 0, lat_bytes, c->stream);
     if (e == hipSuccess) e = launch3_init(c->state(), grid->layout, grid->precision, c->kp, c->lat[0], c->stream);
@@ -244,15 +263,27 @@ lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    for (int64_t k = 0; k < n; ++k) {
+    while (n > 0) {
         const int parity = (int)(c->t & 1);
-        const hipError_t e =
-            c->aa() ? launch3_update(LBM_AA, c->grid.layout, c->grid.precision, c->kp, parity, nullptr, c->lat[0],
-                                     c->obuf, c->stream)
-                    : launch3_update(LBM_NPTL, c->grid.layout, c->grid.precision, c->kp, parity, c->lat[parity],
-                                     c->lat[parity ^ 1], nullptr, c->stream);
+        void* const src = c->lat[c->now];
+        void* const dst = c->lat[c->now ^ 1];
+        hipError_t e;
+        int done = 1;
+        if (c->links && n >= FUSED3 && (!c->aa() || parity == 0)) {
+            e = launch3_fused(c->grid.scheme, c->grid.layout, c->grid.precision, c->kp, src, dst, c->stream);
+            done = FUSED3;
+            c->now ^= 1;
+        } else if (c->aa()) {
+            e = launch3_update(LBM_AA, c->grid.layout, c->grid.precision, c->kp, parity, nullptr, src, c->obuf,
+                               c->stream);
+        } else {
+            e = launch3_update(LBM_NPTL, c->grid.layout, c->grid.precision, c->kp, parity, src, dst, nullptr,
+                               c->stream);
+            c->now ^= 1;
+        }
         if (e != hipSuccess) return c->check(e, "update launch");
-        ++c->t;
+        c->t += done;
+        n -= done;
     }
     return LBM_OK;
 }
@@ -308,9 +339,10 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
         if (e != hipSuccess) return c->check(e, "state upload");
         src = c->readout;
     }
-    // the push form is built from the pull form through a temporary lattice
-    void* tmp = nullptr;
-    if (c->state() == ST_PUSH && hipMalloc(&tmp, (size_t)c->lat_elems * c->elem) != hipSuccess) {
+    // the push form is built from the pull form through a second lattice
+    void* tmp = c->lat[c->now ^ 1];
+    const bool borrow = c->state() == ST_PUSH && !tmp;
+    if (borrow && hipMalloc(&tmp, (size_t)c->lat_elems * c->elem) != hipSuccess) {
         (void)hipGetLastError();
         return c->fail(LBM_ENOMEM, "temporary lattice for the state load");
     }
@@ -318,7 +350,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
                                      c->stream);
     if (e == hipSuccess && c->obuf && c->state() == ST_SWAP)
         e = launch3_aa_outlet_fill(c->grid.layout, c->grid.precision, c->kp, c->cur(), c->obuf, c->stream);
-    if (tmp) {
+    if (borrow) {
         const hipError_t e2 = hipStreamSynchronize(c->stream);
         (void)hipFree(tmp);
         if (e == hipSuccess) e = e2;

@@ -1,6 +1,6 @@
 // k_fused.hip -- several lattice updates per launch, every scheme, layout and
 // storage precision: from one lattice to another, in the state kind the scheme
-// keeps (the one-lattice schemes have a second lattice on grids up to 1 GiB;
+// keeps (the one-lattice schemes have a second lattice on grids up to 1.5 GiB;
 // AA comes here at even update counts, in its push state).
 //
 // One update per launch is bound by memory: 18 stored values move per node and

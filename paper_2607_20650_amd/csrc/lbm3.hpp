@@ -12,6 +12,7 @@
 namespace lbm {
 
 constexpr int Q3 = 19;
+constexpr int FUSED3 = 2; // updates per launch of k3_fused
 
 // In-plane position j of the five vectors with c_z = -1 or +1:
 // (0,-1), (-1,0), (0,0), (1,0), (0,1) as (c_x, c_y).
@@ -53,6 +54,7 @@ struct KParams3 {
     Geometry3 g;
     Physics3 ph;
     const uint8_t* types; // [nz][ny][px]; padding columns are solid
+    const uint32_t* links; // link words [nz][ny][px] (k3_links), or null: single updates only
 };
 
 // Whether the collision layout runs the LDS-staged kernels: 64 x ty tiles

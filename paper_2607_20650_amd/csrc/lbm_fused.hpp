@@ -100,28 +100,28 @@ template <int L, class T> struct Stored {
 // pattern of the scaled magnitude with 12 bits dropped, so a value that stays
 // in registers needs no packing and unpacking: 7 instructions per value instead
 // of 12.  Values that round to the top code (NaN) are rare; one test per node.
-template <class T, class Rng> __device__ __forceinline__ void round_stored(float* f, const Rng& rng)
+template <class T, int Q = 9, class Rng> __device__ __forceinline__ void round_stored(float* f, const Rng& rng)
 {
     if constexpr (std::is_same_v<T, int16_t> || std::is_same_v<T, char16_t>) {
         constexpr uint32_t TOP = 0x07fff000u; // bits of C16_TOP
-        uint32_t a[9], top = 0;
+        uint32_t a[Q], top = 0;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
+        for (int i = 0; i < Q; ++i) {
             const uint32_t m = c16_scaled(f[i]);
             a[i] = (m + (std::is_same_v<T, int16_t> ? 0x7ff + ((m >> 12) & 1) : rng.draw(i) >> 20)) & 0xfffff000u;
             top = max(top, a[i]);
         }
 #pragma unroll
-        for (int i = 0; i < 9; ++i)
+        for (int i = 0; i < Q; ++i)
             f[i] = __builtin_copysignf(__builtin_bit_cast(float, a[i]) * 0x1p112f, f[i]);
         if (__any(top == TOP)) {
             asm volatile("");
 #pragma unroll
-            for (int i = 0; i < 9; ++i) f[i] = a[i] == TOP ? __builtin_nanf("") : f[i];
+            for (int i = 0; i < Q; ++i) f[i] = a[i] == TOP ? __builtin_nanf("") : f[i];
         }
     } else if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) f[i] = ld(enc<T>(f[i], rng.draw(i)));
+        for (int i = 0; i < Q; ++i) f[i] = ld(enc<T>(f[i], rng.draw(i)));
     }
 }
 

@@ -9,6 +9,14 @@
 
 namespace lbm {
 
+// Largest lattice that a one-lattice scheme gets a second one beside, for
+// launches of several updates (a block may not overwrite what its neighbours
+// still read).  Per update, three simulations in turn: AA 4096 x 1024 FP32 53
+// us in place, 21 us between two lattices; NPOL 3001 x 1499 FP32 bundle 69 and
+// 20 us.  1.5 GiB is 1/192 of the device; larger grids, where one lattice is
+// what the scheme is chosen for, keep to single updates in place.
+constexpr size_t SPARE_MOST = (size_t)3 << 29;
+
 // Validate the arguments of one simulation (as lbm_create documents them) and
 // fill geometry (sizes, pitch, tile) and FP32 physics constants.  kp.types is
 // left null.  Returns LBM_OK or LBM_EINVAL with err set.

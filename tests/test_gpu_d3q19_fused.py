@@ -1,0 +1,43 @@
+"""Two D3Q19 updates per launch against single updates, bitwise.
+
+``step(1)`` calls launch the scheme's own kernel; one ``step(n)`` runs two
+updates per launch where it can.  Both do the same operations per node in the
+same order, so every population must be equal bit for bit, on grids that end
+inside a tile or a chunk of planes, on every boundary kind.
+"""
+import numpy as np
+import pytest
+
+from oracle import d3q19 as o3
+from paper_2607_20650_amd import workloads as W
+from tests.helpers import ALL_PRECISIONS
+
+pytestmark = pytest.mark.gpu
+
+P, C, IO = o3.PERIODIC, o3.CLOSED, o3.INFLOW_OUTFLOW
+AXES = [(P, P, P), (C, C, C), (IO, C, P), (IO, P, C), (P, C, P)]
+
+
+@pytest.mark.parametrize("precision", ALL_PRECISIONS)
+@pytest.mark.parametrize("nx,ny,nz", [(70, 67, 71), (5, 260, 260), (2, 400, 420), (323, 1000, 1), (130, 25, 101),
+                                      (420, 400, 2), (1, 600, 600), (60, 73, 74)])
+def test_two_updates_per_launch_bitwise(nx, ny, nz, precision):
+    from paper_2607_20650_amd.lbm import Simulation3
+    flags = W.random_flags3(nx, ny, nz, 0.1, nx + ny)
+    st = W.random_state3(nx, ny, nz, 0.02, seed=5, dtype=np.float32)
+    for k, axes in enumerate(AXES):
+        if axes[0] == IO and nx < 2:
+            continue
+        for scheme, layout in [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "blocked" if k % 2 else "stream")]:
+            out = []
+            for calls in ([1] * 7, [1, 2, 4]):
+                with Simulation3(flags, 0.8, *axes, u_in=(0.05, 0.01, -0.01), g=(1e-4, 2e-4, -1e-4),
+                                 u0=(0.02, 0.0, 0.01), scheme=scheme, layout=layout, precision=precision) as sim:
+                    for n in calls:
+                        sim.step(n)
+                    sim.set_state(st)
+                    for n in calls:
+                        sim.step(n)
+                    out.append(sim.populations())
+            a, b = out
+            assert np.array_equal(a, b, equal_nan=True), (axes, scheme, layout, np.argwhere(a != b)[:3])
