@@ -350,13 +350,17 @@ hipError_t launch3_links(const Geometry3& g, const uint8_t* types, uint32_t* lin
 bool fused3_serves(const Geometry3& g, int layout, int prec)
 {
     // Smaller grids leave most CUs without a block, and a block's planes come
-    // one after another (64 x 64 x 64 FP32 stream pull: 15.5 us per update
-    // either way, FP16S-SR 20.5 against 12.7; 100 x 60 x 80: 20 against 32 us,
-    // FP16S-SR 22 against 27).  The kernel's byte offsets within a plane stay
-    // below OFF_NONE.  The collision layout keeps its staged kernels: a
-    // wavefront's load of one direction is not one run there.
+    // one after another.  Where a side is closed or has an inlet and an outlet,
+    // single updates look up the sources of whole walls: 100 x 60 x 80 FP32
+    // pull 32 against 20 us per update (FP16S-SR 27, 22), 64 x 64 x 64 the same
+    // either way (FP16S-SR 13, 20).  All periodic, they hold out while the
+    // lattices stay in the cache: 128 x 96 x 96 FP32 32 against 38 us, 100 x 200
+    // x 100 77 against 68.  The kernel's byte offsets within a plane stay below
+    // OFF_NONE.  The collision layout keeps its staged kernels: a wavefront's
+    // load of one direction is not one run there.
+    const bool walls = g.xa != AX_PERIODIC || g.ya != AX_PERIODIC || g.za != AX_PERIODIC;
     const int64_t plane = (layout == L_BLOCKED ? g.pstep : g.plane) * (prec == P_FP32 ? 4 : 2);
-    return layout != L_COLLISION && g.plane * g.nz >= 320000 && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
+    return layout != L_COLLISION && g.nx * g.ny * g.nz >= (walls ? 320000 : 1500000) && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
            plane < ((int64_t)1 << 30) && g.plane < ((int64_t)1 << 28);
 }
 
