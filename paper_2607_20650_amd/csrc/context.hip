@@ -89,6 +89,7 @@ struct lbm_ctx {
     bool have_prev = false;
     bool poisoned = false;
     std::string err;
+    HostRing ring;
     int64_t bytes = 0;
     int64_t fluid = 0;
     int device = 0; // device current at lbm_create
@@ -154,6 +155,7 @@ void free_all(lbm_ctx* c)
     c->readout = nullptr;
     c->u_prev = nullptr;
     c->partials = c->dout = nullptr;
+    c->ring.release();
     if (c->cap) (void)hipStreamDestroy(c->cap);
     c->cap = nullptr;
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
@@ -397,8 +399,7 @@ lbm_status lbm::setup_params(const lbm_grid* grid, const uint8_t* flags, double 
         return bad("tile needs more threads than a block of the scheme allows (256; 1024 for the one-lattice "
                    "schemes; 512 for 64-wide collision-layout tiles of the staged kernels)");
     const int64_t N = nx * ny;
-    for (int64_t k = 0; k < N; ++k)
-        if (flags[k] > 1) return bad("flags must be 0 (fluid) or 1 (solid)");
+    if (bad_flags(flags, N)) return bad("flags must be 0 (fluid) or 1 (solid)");
 
     kp.rin = nullptr;
     kp.rout = nullptr;
@@ -672,8 +673,8 @@ lbm_status lbm_macros(lbm_ctx* c, float* rho, float* u, int on_device)
     float* drho = c->readout;
     float* du = c->readout + N;
     hipError_t e = launch_macros(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), drho, du, c->stream);
-    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, drho, N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && u) e = hipMemcpyAsync(u, du, 2 * N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess && rho) e = c->ring.to_host(rho, drho, N * sizeof(float), c->stream);
+    if (e == hipSuccess && u) e = c->ring.to_host(u, du, 2 * N * sizeof(float), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return c->check(e, "macros readout");
 }
@@ -691,7 +692,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, float* f, int on_device)
     if (st != LBM_OK) return st;
     hipError_t e = launch_get_populations(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                                           c->readout, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(f, c->readout, 9 * N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess) e = c->ring.to_host(f, c->readout, 9 * N * sizeof(float), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return c->check(e, "populations readout");
 }

@@ -51,6 +51,7 @@ struct lbm3_ctx {
     int64_t lat_elems = 0;
     int64_t t = 0;
     int now = 0; // the lattice that holds the state
+    HostRing ring;
     bool poisoned = false;
     std::string err;
 
@@ -85,6 +86,7 @@ void free3(lbm3_ctx* c)
     c->types = nullptr;
     c->links = nullptr;
     c->readout = nullptr;
+    c->ring.release();
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     c->stream = nullptr;
 }
@@ -156,8 +158,7 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
     const int64_t max_threads = grid->layout == LBM_COLLISION && aos3_staged(px3, ny, tx, ty) ? 512 : 256;
     if ((int64_t)tx * ty > max_threads) return bad("tile needs more than 256 threads (512 for 64-wide collision-layout tiles)");
     const int64_t N = nx * ny * nz;
-    for (int64_t k = 0; k < N; ++k)
-        if (flags[k] > 1) return bad("flags must be 0 (fluid) or 1 (solid)");
+    if (bad_flags(flags, N)) return bad("flags must be 0 (fluid) or 1 (solid)");
 
     lbm3_ctx* c = new (std::nothrow) lbm3_ctx();
     if (!c) return create3_error(LBM_ENOMEM, "host allocation failed");
@@ -302,8 +303,8 @@ lbm_status lbm3_macros(lbm3_ctx* c, float* rho, float* u, int on_device)
     float* dr = c->readout;
     float* du = c->readout + N;
     hipError_t e = launch3_macros(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(), dr, du, c->stream);
-    if (e == hipSuccess && rho) e = hipMemcpyAsync(rho, dr, N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess && u) e = hipMemcpyAsync(u, du, 3 * N * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess && rho) e = c->ring.to_host(rho, dr, N * sizeof(float), c->stream);
+    if (e == hipSuccess && u) e = c->ring.to_host(u, du, 3 * N * sizeof(float), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return c->check(e, "macros readout");
 }
@@ -321,7 +322,7 @@ lbm_status lbm3_get_populations(lbm3_ctx* c, float* f, int on_device)
     hipError_t e = launch3_get_populations(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(),
                                            c->readout, c->stream);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(f, c->readout, (size_t)c->nodes() * Q3 * sizeof(float), hipMemcpyDeviceToHost, c->stream);
+        e = c->ring.to_host(f, c->readout, (size_t)c->nodes() * Q3 * sizeof(float), c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     return c->check(e, "populations readout");
 }

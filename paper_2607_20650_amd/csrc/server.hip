@@ -238,9 +238,7 @@ lbm_status finish_oldest(lbm_server* s, bool blocking)
         const float* res = (const float*)(s->h_res + r->res_off);
         r->rho.assign(res, res + N);
         r->u.assign(res + N, res + 3 * N);
-        r->status = LBM_OK;
-        for (int64_t k = 0; k < 2 * N && r->status == LBM_OK; ++k)
-            if (!std::isfinite(r->u[k])) r->status = LBM_EUNSTABLE;
+        r->status = all_finite(res + N, 2 * N) ? LBM_OK : LBM_EUNSTABLE;
         r->res_off = -1;
         r->state = Q_DONE;
         s->unreported.push_back(r->id);
