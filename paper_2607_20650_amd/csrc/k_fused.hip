@@ -234,12 +234,14 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // Strips: chunks of rows that make at most 1024 blocks, four per CU, all
     // resident at once: one round, few recomputed rows at the chunks' ends
     // (4096 x 1024 FP32: 21.4 us per update; 768 blocks 23.0, 512 27.2, 1280
-    // 24.1); at most 128 rows.
+    // 24.1); at most 128 rows.  Of the FP32 push form three per CU are resident
+    // (the same grid: 768 blocks 24.8, 1024 26.5).
     q.kk = (int)std::min<int64_t>(prec == P_FP32 ? fused_most<float>() : fused_most<uint16_t>(), g.ny);
     if (scheme == S_AA) q.kk &= ~1;
     if (q.kk < 2) return FusedPlan{};
+    const bool push = scheme == S_PUSH || scheme == S_AA;
     const int64_t w = (int64_t)(64 - 2 * q.kk) * FUSED_WAVES, cols = (g.nx + w - 1) / w;
-    const int64_t chunks = std::max<int64_t>(1024 / cols, 1);
+    const int64_t chunks = std::max<int64_t>((push && prec == P_FP32 ? 768 : 1024) / cols, 1);
     const int64_t rows = (g.ny + chunks - 1) / chunks;
     q.rows = (int)std::min<int64_t>(std::max<int64_t>(rows, 12), 128);
     return q;
