@@ -236,7 +236,12 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // (4096 x 1024 FP32: 21.4 us per update; 768 blocks 23.0, 512 27.2, 1280
     // 24.1); at most 128 rows.  Of the FP32 push form three per CU are resident
     // (the same grid: 768 blocks 24.8, 1024 26.5).
-    q.kk = (int)std::min<int64_t>(prec == P_FP32 ? fused_most<float>() : fused_most<uint16_t>(), g.ny);
+    // FP32 up to 3 million nodes: six updates per launch, where the chunks are
+    // so short that the rows recomputed for eight cost more than two launches
+    // less (1600 x 700: 5.9 against 6.4 us per update, alone 11.0 against 12.8;
+    // 1000 x 2600: 12.8, 13.5; 4096 x 1024: 17.3, 16.7).
+    const int most = prec != P_FP32 ? fused_most<uint16_t>() : g.nx * g.ny <= 3000000 ? 6 : fused_most<float>();
+    q.kk = (int)std::min<int64_t>(most, g.ny);
     if (scheme == S_AA) q.kk &= ~1;
     if (q.kk < 2) return FusedPlan{};
     const bool push = scheme == S_PUSH || scheme == S_AA;
