@@ -68,13 +68,16 @@ __global__ void __launch_bounds__(64 * FUSED_WAVES, S != ST_PUSH || sizeof(T) ==
 }
 
 // ------------------------------------------------------------------ tiles
-// The same updates for small grids: a block holds a tile of 64 columns and
-// TILE_ROWS rows, one node per thread, and does kk updates on it; the c_y != 0
+// The same updates for small grids: a block holds a tile of 32 x 32 nodes, one
+// per thread (two rows per wavefront), and does kk updates on it; the c_y != 0
 // values pass between the rows through LDS (one barrier per update, two
 // buffers), the others between lanes.  A launch waits for memory once and for
 // one chain of kk collisions, where k_fused waits for rows one after another.
-// The tile loses a ring of one node per update, recomputed by its neighbours.
-constexpr int TILE_ROWS = 16; // 1024 threads
+// The tile loses a ring of one node per update, recomputed by its neighbours;
+// 32 x 32 loses less than 64 x 16 (513 x 257: 1.85 us per update for 4 per
+// launch, 2.13 for 3 of 64 x 16).  An update of a tile takes about 0.6 us, the
+// VALU issue of 16 wavefronts; a launch 3 - 4 us besides.
+constexpr int TILE_X = 32, TILE_ROWS = 32; // 1024 threads
 
 template <int L, class T, int S>
 __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restrict__ src, T* __restrict__ dst, int kk,
@@ -82,18 +85,19 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
 {
     using R = Stored<L, T>;
     constexpr int E = (int)sizeof(T) * lat_stride<L>();
-    __shared__ float smem_tile[2 * 6 * 64 * TILE_ROWS]; // [2][6][rows][64]: directions 0..2 and 6..8
+    __shared__ float smem_tile[2 * 6 * TILE_X * TILE_ROWS]; // [2][6][rows][columns]: directions 0..2 and 6..8
     const Geometry& g = p.g;
     const int nx = (int)g.nx, ny = (int)g.ny;
     constexpr int H = TILE_ROWS;
     const int w = (int)__builtin_amdgcn_readfirstlane(threadIdx.y), lane = (int)threadIdx.x;
+    const int col = lane % TILE_X, line = 2 * w + lane / TILE_X; // of the tile
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x);
     const int chunk = (int)(t / (uint32_t)strips), strip = (int)(t - (uint32_t)chunk * (uint32_t)strips);
-    const int x0 = strip * (64 - 2 * kk), y0 = chunk * (H - 2 * kk), y = y0 - kk + w;
+    const int x0 = strip * (TILE_X - 2 * kk), y0 = chunk * (H - 2 * kk), y = y0 - kk + line;
     // column and row wrapped on a periodic axis; past any other side the last
     // ones stand in (nothing valid is taken from them)
-    int x = x0 - kk + lane;
-    const bool keep = lane >= kk && lane < 64 - kk && x < nx && w >= kk && w < H - kk && y < ny;
+    int x = x0 - kk + col;
+    const bool keep = col >= kk && col < TILE_X - kk && x < nx && line >= kk && line < H - kk && y < ny;
     if (g.xa == AX_PERIODIC) {
         if (x < 0 || x >= nx) x = ((x % nx) + nx) % nx;
     } else {
@@ -107,14 +111,13 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
     }
     const int64_t pitch = g.px * E;
     const int64_t plane = (int64_t)R::D * g.P * (int)sizeof(T);
-    const uint32_t off = (uint32_t)x * (uint32_t)E;
+    const uint32_t off = (uint32_t)r * (uint32_t)pitch + (uint32_t)x * (uint32_t)E;
     R e;
-    e.load(as_global((const char*)src + r * pitch), plane, off);
+    e.load(as_global((const char*)src), plane, off);
     const uint32_t node = (uint32_t)r * (uint32_t)g.px + (uint32_t)x;
     const uint32_t type = p.types[node];
-    const uint32_t lk =
-        __builtin_amdgcn_raw_buffer_load_b32(buffer_at(const_cast<uint32_t*>(p.links) + (int64_t)r * g.px),
-                                             (type & IRREGULAR) ? (uint32_t)x * 4u : OFF_NONE, 0, 0);
+    const uint32_t lk = __builtin_amdgcn_raw_buffer_load_b32(buffer_at(const_cast<uint32_t*>(p.links)),
+                                                             (type & IRREGULAR) ? node * 4u : OFF_NONE, 0, 0);
     const bool inout = g.xa == AX_INOUT, outlet = g.zh && x == nx - 1;
     const bool some = __any(lk != 0), fix = __any(outlet);
     const float ein[3] = {inlet_value(p, 2), inlet_value(p, 5), inlet_value(p, 8)};
@@ -141,24 +144,25 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
         }
         fix_outlet();
     }
-    constexpr int row = 64 * H; // values per direction
+    constexpr int row = TILE_X * H; // values per direction
 #pragma unroll 1
     for (int l = 0; l < kk; ++l) {
         if constexpr (S == ST_PUSH) {
-            if (w >= l && w <= H - 1 - l) collide_node();
+            if (2 * w + 1 >= l && 2 * w <= H - 1 - l) collide_node();
         }
         float* b = smem_tile + (l & 1) * 6 * row + 64 * w + lane;
 #pragma unroll
         for (int k = 0; k < 3; ++k) b[k * row] = f[k], b[(3 + k) * row] = f[6 + k];
         __syncthreads();
-        // rows up to l past the tile's edge hold no valid inflow any more
-        const bool live = w > l && w < H - 1 - l;
+        // rows up to l from the tile's edge hold no valid inflow any more
+        const bool live = 2 * w + 1 > l && 2 * w < H - 1 - l;
         if (!live) continue;
         const float w3 = from_right(f[3]), w5 = from_left(f[5]);
-        // a row's neighbours: below (w - 1) for c_y = +1, above for c_y = -1;
-        // a column past the tile's edge reads another row's value, unused
-        const float n0 = b[64 + 1], n1 = b[row + 64], n2 = b[2 * row + 64 - 1];
-        const float n6 = b[3 * row - 64 + 1], n7 = b[4 * row - 64], n8 = b[5 * row - 64 - 1];
+        // a row's neighbours: below for c_y = +1, above for c_y = -1; past the
+        // tile's edge another row's or direction's value is read, unused
+        constexpr int X = TILE_X;
+        const float n0 = b[X + 1], n1 = b[row + X], n2 = b[2 * row + X - 1];
+        const float n6 = b[3 * row - X + 1], n7 = b[4 * row - X], n8 = b[5 * row - X - 1];
         float q[9] = {n0, n1, n2, w3, f[4], w5, n6, n7, n8};
         if (some) {
             keep_branch();
@@ -172,11 +176,11 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
             by_solid<8>(lk, q[8], f[0]);
             if (inout) {
                 keep_branch();
-                by_side<0>(lk, q[0], b[64]);
+                by_side<0>(lk, q[0], b[X]);
                 by_side<2>(lk, q[2], ein[0]);
                 by_side<3>(lk, q[3], f[3]);
                 by_side<5>(lk, q[5], ein[1]);
-                by_side<6>(lk, q[6], b[3 * row - 64]);
+                by_side<6>(lk, q[6], b[3 * row - X]);
                 by_side<8>(lk, q[8], ein[2]);
             }
         }
@@ -195,7 +199,7 @@ __global__ void __launch_bounds__(1024) k_fused_tile(KParams p, const T* __restr
 #pragma unroll
         for (int i = 0; i < 9; ++i) e.v[i] = 0u;
     }
-    e.store((char*)dst + r * pitch, plane, keep ? off : OFF_NONE);
+    e.store((char*)dst, plane, keep ? off : OFF_NONE);
 }
 
 FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
@@ -209,22 +213,22 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     if (g.fw || p.rin != nullptr || g.px * stride * elem >= ((int64_t)1 << 30))
         return q;
     auto tiles = [&](int kk) {
-        const int w = 64 - 2 * kk, h = TILE_ROWS - 2 * kk;
+        const int w = TILE_X - 2 * kk, h = TILE_ROWS - 2 * kk;
         return ((g.nx + w - 1) / w) * ((g.ny + h - 1) / h);
     };
-    // Small grids: tiles, with as many updates per launch as leave at most one
-    // block per CU (128 x 64: 6.1 us per update for single updates, 1.14 us for
-    // 7 per launch; 513 x 257: 4.4 and 2.2 us for 3 per launch).  Larger grids
-    // stay with 3 up to about 700,000 nodes, beyond which the columns and rows
-    // the tiles recompute cost more than the strips' serial rows (1000 x 601:
-    // 6.1 against 7.2 us; 1600 x 700: 9.2 against 9.8 us, and 8.1 against 5.3
-    // with other simulations beside it).
-    if (g.nx * g.ny <= 700000) {
+    // Small grids: tiles, with as many updates per launch, up to 12, as leave at
+    // most one block per CU (per update, alone: 128 x 64 6.1 us for single
+    // updates, 1.14 for 12 per launch; 513 x 257 4.4, 1.85 for 4 per launch).
+    // Larger grids stay with 4 up to 1.6 million nodes, beyond which the nodes
+    // the tiles recompute cost more than the strips' serial rows (FP32, alone
+    // and with two simulations beside: 1000 x 900 5.9, 4.4 against 10.1, 4.5 us
+    // in strips; 1600 x 1000 8.5, 8.0 against 12.5, 7.7; 2048 x 2048 in strips
+    // 24, 19).
+    if (g.nx * g.ny <= 1600000) {
         q.tile = 1;
         const int unit = scheme == S_AA ? 2 : 1; // AA's updates come in pairs
-        q.kk = 7 / unit * unit;
+        q.kk = 12;
         while (q.kk > 4 && tiles(q.kk) > 256) q.kk -= unit;
-        if (unit == 1 && tiles(q.kk) > 256) q.kk = 3;
         return q;
     }
     // FP16C on lattices that fit the 256 MB cache is bound by its codec either
@@ -238,8 +242,8 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // (the same grid: 768 blocks 24.8, 1024 26.5).
     // FP32 up to 3 million nodes: six updates per launch, where the chunks are
     // so short that the rows recomputed for eight cost more than two launches
-    // less (1600 x 700: 5.9 against 6.4 us per update, alone 11.0 against 12.8;
-    // 1000 x 2600: 12.8, 13.5; 4096 x 1024: 17.3, 16.7).
+    // less (6000 x 400 bundle: 10.6 against 11.2 us per update, alone 14.4
+    // against 17.6; 1000 x 2600: 12.8, 13.5; 4096 x 1024: 17.3, 16.7).
     const int most = prec != P_FP32 ? fused_most<uint16_t>() : g.nx * g.ny <= 3000000 ? 6 : fused_most<float>();
     q.kk = (int)std::min<int64_t>(most, g.ny);
     if (scheme == S_AA) q.kk &= ~1;
@@ -256,7 +260,7 @@ hipError_t launch_fused(int scheme, int layout, int prec, const KParams& p, cons
                         void* dst, hipStream_t s)
 {
     if (kk < 1 || kk > q.kk) return hipErrorInvalidValue;
-    const int w = 64 - 2 * kk;
+    const int w = (q.tile ? TILE_X : 64) - 2 * kk;
     const int64_t cols = q.tile ? (p.g.nx + w - 1) / w : (p.g.nx + w * FUSED_WAVES - 1) / (w * FUSED_WAVES);
     const int rows = q.tile ? TILE_ROWS - 2 * kk : q.rows;
     const int64_t blocks = cols * ((p.g.ny + rows - 1) / rows);
@@ -267,7 +271,7 @@ hipError_t launch_fused(int scheme, int layout, int prec, const KParams& p, cons
         auto go = [&](auto S) {
             constexpr int SV = decltype(S)::value;
             if (q.tile)
-                hipLaunchKernelGGL((k_fused_tile<LV, T, SV>), dim3((uint32_t)blocks), dim3(64, TILE_ROWS),
+                hipLaunchKernelGGL((k_fused_tile<LV, T, SV>), dim3((uint32_t)blocks), dim3(64, TILE_X * TILE_ROWS / 64),
                                    0, s, p, (const T*)src, (T*)dst, kk, (int)cols);
             else
                 hipLaunchKernelGGL((k_fused<LV, T, SV>), dim3((uint32_t)blocks), dim3(64, FUSED_WAVES), 0, s, p,

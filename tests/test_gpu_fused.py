@@ -50,18 +50,20 @@ def test_small_grids_bitwise(nx, ny, precision):
 
 
 @pytest.mark.parametrize("precision", ALL_PRECISIONS)
-@pytest.mark.parametrize("nx,ny", [(1009, 701), (193, 3700), (90001, 8), (180000, 4), (13, 60001)])
+@pytest.mark.parametrize("nx,ny", [(2311, 701), (193, 8300), (200003, 9), (410001, 4), (13, 125003)])
 def test_large_grids_bitwise(nx, ny, precision):
     _compare(nx, ny, AXES[:4], ["NPTL", "PUSH"], ["stream"], [precision], calls=(8, 5, 17))
 
 
 def test_large_grid_layouts_bitwise():
-    _compare(1011, 707, AXES[2:4], ["LPTL", "NPTL", "PUSH"], ["bundle", "collision"], ["fp32", "fp16sr", "fp16c"],
+    _compare(2311, 701, AXES[2:4], ["LPTL", "NPTL", "PUSH"], ["bundle", "collision"], ["fp32", "fp16sr", "fp16c"],
              calls=(8, 5))
+    # FP32 from 3 million nodes on: eight updates per launch
+    _compare(3011, 1003, AXES[1:4], ["NPTL", "PUSH", "AA", "NSOL"], ["stream"], ["fp32"], calls=(16, 13))
 
 
 @pytest.mark.parametrize("precision", ALL_PRECISIONS)
-@pytest.mark.parametrize("nx,ny", [(128, 64), (37, 20), (5, 3), (57, 5), (200, 101), (1009, 701), (90001, 8), (13, 60001)])
+@pytest.mark.parametrize("nx,ny", [(128, 64), (37, 20), (5, 3), (57, 5), (200, 101), (2311, 701), (200003, 9), (13, 125003)])
 def test_one_lattice_schemes_bitwise(nx, ny, precision):
     """AA in pairs of updates, NPOL and NSOL without their edge buffers, from
     odd and even update counts, and back to single updates in between."""
