@@ -233,7 +233,7 @@ lbm_status lbm_get_info(const lbm_ctx* ctx, lbm_info* info);
 
 /* lbm_set_bundle -- updates per cached HIP graph used by lbm_step; a launch does
  * as many of them as suit the grid (the result is bitwise that of single
- * updates).  0 = one launch of the scheme's own kernel per update, no graph.
+ * updates), and bundles of four launches or fewer are launched directly.  0 = one launch of the scheme's own kernel per update, no graph.
  * Default 32. */
 lbm_status lbm_set_bundle(lbm_ctx* ctx, int32_t k);
 

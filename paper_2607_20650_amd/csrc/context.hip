@@ -285,17 +285,20 @@ lbm_status launch_one(lbm_ctx* c, int parity, int cur, hipStream_t s)
 // n updates on stream s from update count t on, the state in lattice cur
 // (cur moves along): in as few launches as `most` updates per launch allow,
 // evenly filled.  AA's two kinds of update make pairs: an odd count starts or
-// ends with a single one.
+// ends with a single one.  Strips take even numbers while they can: 50 columns
+// of 64 kept instead of 52 or 48 put the seams of rows off 16-byte boundaries
+// (3001 x 1499 FP32 bundle, 50 updates as 8, 7, 7, ...: 25.5 us per update; as
+// 8, 8, 8, 8, 6, 6, 6: 23.5).
 lbm_status launch_updates(lbm_ctx* c, int64_t t, int64_t n, int most, int& cur, hipStream_t s)
 {
-    const int unit = c->grid.scheme == S_AA ? 2 : 1;
-    const bool two = is_two_lattice(c->grid.scheme);
+    const bool aa = c->grid.scheme == S_AA, two = is_two_lattice(c->grid.scheme);
     for (int64_t left = n; left > 0;) {
         const int64_t now = t + n - left;
         int kk = 1;
-        if (most > 1 && now % unit == 0 && left >= unit) {
-            const int64_t units = left / unit, launches = (units * unit + most - 1) / most;
-            kk = (int)((units + launches - 1) / launches) * unit;
+        if (most > 1 && !(aa && ((now & 1) || left == 1))) {
+            const int64_t launches = (left + most - 1) / most;
+            kk = (int)((left + launches - 1) / launches);
+            if ((aa || !c->plan.tile) && (kk & 1)) kk += kk < std::min<int64_t>(most, left) ? 1 : aa ? -1 : 0;
         }
         // the edge buffers are not kept up to date between fused launches
         const bool fused = kk > 1 || (most > 1 && has_buffer_grid(c->grid.scheme));
@@ -617,7 +620,12 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
         if (e != hipSuccess) return c->check(e, "edge fill");
         c->edges_old = false;
     }
-    while (c->bundle > 0 && n >= c->bundle) {
+    // A graph of few launches costs the host more than they do: 128 x 64, 200
+    // updates as 6 graphs of 3 launches and one more 207 us, as 17 launches
+    // 171; graphs of 8 launches save up to 40 % beside other simulations (513 x
+    // 257, 96 updates: 100 against 117 - 142 us).
+    const bool graphs = c->bundle > 4 * (int64_t)most;
+    while (graphs && n >= c->bundle) {
         const int key = graph_key(c);
         if (!c->gexec[key]) {
             lbm_status st = build_graph(c, key);
