@@ -18,10 +18,9 @@
 // thread and 16 wavefronts need more than the 128 registers they may have.
 // Per update, three simulations in turn: 201 x 97 x 85 AA FP32 stream 104 us
 // in place one by one, 55 us here; 230 x 140 x 200 FP16S stream pull 302 and
-// 125 us; 256^3 FP32 blocked pull 520 and 430 us (alone 512 and 436), where a
-// block's plane takes 6.6 us: 4 us of VALU work (a quarter of it on columns
-// past the grid, 256 being 4.3 times 60) and about 1.2 us each of exposed loads
-// and stores.  Stores of four columns gathered through LDS (10 instead of 38
+// 125 us; 256^3 FP32 blocked pull 520 and 445 us (alone 512 and 402), where a
+// block's plane takes 6 us: 4 us of VALU work (a fifth of it on columns past
+// the grid, 256 being 4.3 times 60), the rest exposed loads and stores.  Stores of four columns gathered through LDS (10 instead of 38
 // per plane) lost 20 %.
 #include <algorithm>
 
@@ -124,17 +123,14 @@ __global__ void __launch_bounds__(TILE3_X* TILE3_Y / 2) k3_fused(KParams3 p, con
     auto next_plane = [&](int z) { return z + 1 < nz ? z + 1 : (zper ? 0 : nz - 1); };
 
     uint32_t nv[R][Q3], nlk[R], nty[R]; // the plane sent for, its link words, and the types of the plane after it
-    auto send = [&](int z) {
+    auto send = [&](int z, int j) {
         const gptr<const char> a = as_global((const char*)src + z * planep);
 #pragma unroll
         for (int i = 0; i < Q3; ++i) {
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                if constexpr (E == 4)
-                    nv[j][i] = *(gptr<const uint32_t>)(a + i * dirp + off[j]);
-                else
-                    nv[j][i] = *(gptr<const uint16_t>)(a + i * dirp + off[j]);
-            }
+            if constexpr (E == 4)
+                nv[j][i] = *(gptr<const uint32_t>)(a + i * dirp + off[j]);
+            else
+                nv[j][i] = *(gptr<const uint16_t>)(a + i * dirp + off[j]);
         }
     };
     auto send_links = [&](int z) { // where the type marks the node irregular; other lanes get 0
@@ -160,7 +156,8 @@ __global__ void __launch_bounds__(TILE3_X* TILE3_Y / 2) k3_fused(KParams3 p, con
     };
     int zn = wrap_z(zs);
     send_types(zn);
-    send(zn);
+    send(zn, 0);
+    send(zn, 1);
     send_links(zn);
     zn = next_plane(zn);
     send_types(zn);
@@ -196,8 +193,8 @@ __global__ void __launch_bounds__(TILE3_X* TILE3_Y / 2) k3_fused(KParams3 p, con
             lk[j][0] = nlk[j];
         }
         any = (any << 1) | (__any((nlk[0] | nlk[1]) != 0) ? 1u : 0u);
-        auto send_next = [&]() {
-            send(zn);
+        auto send_rest = [&]() {
+            send(zn, 1);
             send_links(zn);
             zn = next_plane(zn);
             send_types(zn);
@@ -211,10 +208,13 @@ __global__ void __launch_bounds__(TILE3_X* TILE3_Y / 2) k3_fused(KParams3 p, con
                 round_stored<T, Q3>(f[j], rng);
             }
         };
-        // The pull streams plane z at once and sends for the next one into its
-        // registers; the push form collides first.
+        // The first row of the next plane is sent for at once.  The pull streams
+        // plane z first and sends for the second row then: 38 stores are still
+        // on their way, and 63 accesses may be (both rows at once 451 us per
+        // update on the 256^3 pull, both after streaming 420, this 402).
+        send(zn, 0);
         if constexpr (S == ST_PUSH) {
-            send_next();
+            send_rest();
             if (side) { // values fed by the inlet
                 keep_branch();
 #pragma unroll
@@ -315,7 +315,7 @@ __global__ void __launch_bounds__(TILE3_X* TILE3_Y / 2) k3_fused(KParams3 p, con
                 for (int i = 0; i < Q3; ++i) f[j][i] = q[j][i];
             }
             if constexpr (S != ST_PUSH) {
-                if (l == 0) send_next();
+                if (l == 0) send_rest();
                 collide_plane(l + 1);
             }
         }
