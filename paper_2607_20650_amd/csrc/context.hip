@@ -81,6 +81,7 @@ struct lbm_ctx {
     int cur = 0;    // the lattice that holds the state
     bool edges_old = false; // one-lattice tiled schemes: edge[] is not that of the state
     FusedPlan plan; // several updates per launch
+    bool direct = false; // no graphs: calls have been captured
     int32_t bundle = 32;
     int32_t block = 256;
     hipGraph_t graph[4] = {}; // by graph_key
@@ -612,6 +613,13 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
+    // A captured call is replayed on the lattice it was captured with, so from
+    // the first one on the context does single updates, which leave the state
+    // where they found it after every even number, and bundles by direct launch.
+    if (c->plan.kk > 1 && capturing(c->stream)) {
+        c->plan = FusedPlan{};
+        c->direct = true;
+    }
     const int most = c->bundle > 0 ? c->plan.kk : 1;
     if (n > 0 && c->edge_elems && most > 1) c->edges_old = true;
     if (n > 0 && c->edges_old && most == 1) {
@@ -624,7 +632,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     // updates as 6 graphs of 3 launches and one more 207 us, as 17 launches
     // 171; graphs of 8 launches save up to 40 % beside other simulations (513 x
     // 257, 96 updates: 100 against 117 - 142 us).
-    const bool graphs = c->bundle > 4 * (int64_t)most;
+    const bool graphs = !c->direct && c->bundle > 4 * (int64_t)most;
     while (graphs && n >= c->bundle) {
         const int key = graph_key(c);
         if (!c->gexec[key]) {

@@ -51,6 +51,7 @@ struct lbm3_ctx {
     int64_t lat_elems = 0;
     int64_t t = 0;
     int now = 0; // the lattice that holds the state
+    bool several = false; // FUSED3 updates per launch
     HostRing ring;
     bool poisoned = false;
     std::string err;
@@ -241,6 +242,7 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
         if (!extra) (void)hipGetLastError();
     }
     c->kp.links = c->links;
+    c->several = c->links != nullptr;
     hipError_t e = hipMemcpyAsync(dflags, flags, (size_t)N, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = launch3_types(g, dflags, c->types, c->stream);
     if (e == hipSuccess && c->links) e = launch3_links(g, c->types, c->links, c->stream);
@@ -264,13 +266,17 @@ lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
+    // a captured call is replayed on the lattice it was captured with: from the
+    // first one on single updates, which leave the state where they found it
+    // after every even number
+    if (c->several && capturing(c->stream)) c->several = false;
     while (n > 0) {
         const int parity = (int)(c->t & 1);
         void* const src = c->lat[c->now];
         void* const dst = c->lat[c->now ^ 1];
         hipError_t e;
         int done = 1;
-        if (c->links && n >= FUSED3 && (!c->aa() || parity == 0)) {
+        if (c->several && n >= FUSED3 && (!c->aa() || parity == 0)) {
             e = launch3_fused(c->grid.scheme, c->grid.layout, c->grid.precision, c->kp, src, dst, c->stream);
             done = FUSED3;
             c->now ^= 1;

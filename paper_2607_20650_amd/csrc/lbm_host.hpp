@@ -32,6 +32,13 @@ int64_t lattice_elems(const Geometry& g, int layout);
 // Fluid + outlet nodes of a flag array.
 int64_t count_updated(const lbm_grid* grid, const uint8_t* flags, const lbm_bc* bc);
 
+// Whether the caller is capturing the stream.
+inline bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+}
+
 // Whether any flag is neither 0 nor 1.  No early exit, so that it vectorises.
 inline bool bad_flags(const uint8_t* flags, int64_t n)
 {

@@ -45,3 +45,28 @@ def test_two_updates_per_launch_bitwise(nx, ny, nz, precision):
                     out.append(sim.populations())
             a, b = out
             assert np.array_equal(a, b, equal_nan=True), (axes, scheme, layout, np.argwhere(a != b)[:3])
+
+
+@pytest.mark.parametrize("scheme", ["NPTL", "AA"])
+def test_captured_steps_replay_3d(scheme):
+    """As for the 2-D schemes: a captured even number of updates can be
+    replayed between eager ones."""
+    import torch
+    from paper_2607_20650_amd.lbm import Simulation3
+    flags = W.random_flags3(130, 50, 60, 0.1, 4)
+    kw = dict(u_in=(0.05, 0.01, 0.0), u0=(0.02, 0.0, 0.0), scheme=scheme)
+    with Simulation3(flags, 0.8, IO, C, C, **kw) as sim, Simulation3(flags, 0.8, IO, C, C, **kw) as ref:
+        sim.step(6)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=sim.stream):
+            sim.step(2)
+        done = 6
+        for _ in range(3):
+            with torch.cuda.stream(sim.stream):
+                g.replay()
+            torch.cuda.synchronize()
+            sim.step(4)
+            for _ in range(done + 6):
+                ref.step(1)
+            done = 0
+            assert np.array_equal(sim.populations(), ref.populations()), scheme

@@ -91,3 +91,31 @@ def test_one_lattice_schemes_bitwise(nx, ny, precision):
                         out.append((a, sim.populations()))
                 for a, b in zip(*out):
                     assert np.array_equal(a, b, equal_nan=True), (nx, ny, xa, ya, kw, np.argwhere(a != b)[:3])
+
+
+@pytest.mark.parametrize("scheme", ["NPTL", "PUSH", "AA", "NPOL", "NSOL"])
+def test_captured_steps_replay(scheme):
+    """A captured call of an even number of updates can be replayed, with eager
+    steps and readouts in between: it finds the state where it left it."""
+    import torch
+    from paper_2607_20650_amd.lbm import Simulation
+    flags = W.random_flags(200, 101, 0.1, 4)
+    st = W.random_state(200, 101, 0.02, 3, dtype=np.float32)
+    kw = dict(u_in=(0.05, 0.01), u0=(0.02, 0.0), scheme=scheme)
+    with Simulation(flags, 0.8, INFLOW_OUTFLOW, CLOSED, **kw) as sim, \
+            Simulation(flags, 0.8, INFLOW_OUTFLOW, CLOSED, bundle=0, **kw) as ref:
+        for s in (sim, ref):
+            s.set_state(st)
+            s.step(36)  # several updates per launch so far
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=sim.stream):
+            sim.step(2)
+        for k in range(4):
+            with torch.cuda.stream(sim.stream):
+                g.replay()
+            torch.cuda.synchronize()
+            ref.step(2)
+            assert np.array_equal(sim.populations(), ref.populations()), (scheme, k)
+            sim.step(34)
+            ref.step(34)
+            assert np.array_equal(sim.populations(), ref.populations()), (scheme, k)
