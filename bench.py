@@ -11,8 +11,10 @@ device synchronisation and timed with HIP events on the library's stream.
 
 Also reported on the same JSON line:
   * every scheme x layout x precision variant (median of repeated runs),
-  * roofline of the dominant update kernel (algorithmic bytes per launch over
-    the measured average launch duration, against the 8 TB/s HBM peak),
+  * roofline of the dominant update kernel (algorithmic bytes per update, one
+    read and one write of the lattice, over the measured time per update,
+    against the 8 TB/s HBM peak; a launch of several updates moves the lattice
+    once for all of them, so this can exceed the peak),
   * the FP64 CPU oracle timed on the host cores on a bounded sample,
   * an off-cache reference grid and the 2^31-node memory-limit grid,
   * batched-serving latency and throughput when the serving engine is built.
@@ -77,9 +79,13 @@ def accuracy(lbm, sc, scheme, layout, prec, g):
 
 def kernel_name(scheme, layout, precision, tile_x):
     """Update kernel the library launches for a variant on this workload (the
-    dispatch rules of the HIP sources: one-wavefront-wide NPOL tiles take the
-    lean kernel; 64-wide collision-layout tiles of the two-lattice pull, of AA
-    and of the FP32 push take the LDS-staged kernels)."""
+    dispatch rules of the HIP sources: FP32 and FP16S(-SR) do several updates
+    per launch in k_fused; FP16C lattices that fit the Infinity Cache take the
+    schemes' own kernels, where one-wavefront-wide NPOL tiles take the lean
+    kernel and 64-wide collision-layout tiles of the two-lattice pull, of AA
+    and of the FP32 push the LDS-staged ones)."""
+    if not precision.startswith("fp16c"):
+        return "k_fused"
     staged = layout == "collision" and tile_x == 64
     if scheme == "NPOL":
         return "k_npol64" if tile_x == 64 else "k_npol"
@@ -226,8 +232,8 @@ def hbm_reference(torch, lbm, workloads, log, headline, steps=100):
     """A grid far beyond the 256 MB Infinity Cache (16000 x 8000 channel,
     9.2 GB two-lattice FP32, 4.6 GB one-lattice): the headline variant and
     the best two- and one-lattice variants there show what HBM itself
-    sustains.  Each kernel launch is one update, so the event time per update
-    is the average launch duration."""
+    sustains: the one-lattice schemes update it in place, one update per
+    launch, the two-lattice ones do several per launch."""
     sc = workloads.channel(nx=16000, ny=8000)
     out = {"workload": f"channel-{sc.nx}x{sc.ny}", "steps": steps, "variants": {}}
     runs = [("NPTL", "stream"), ("AA", "stream"), ("NPOL", "bundle")]
@@ -243,7 +249,7 @@ def hbm_reference(torch, lbm, workloads, log, headline, steps=100):
         gbs = mlups * 1e6 * 72 / 1e9
         out["variants"][f"{scheme}/{layout}/fp32"] = {
             "mlups": round(mlups, 1), "algorithmic_gbs": round(gbs, 1), "frac_of_8tbs": round(gbs / HBM_PEAK_GBS, 4),
-            "avg_launch_us": round(ms * 1e3 / steps, 2), "device_gb": round(lat_gb, 2)}
+            "update_us": round(ms * 1e3 / steps, 2), "device_gb": round(lat_gb, 2)}
         log(f"hbm reference {sc.nx}x{sc.ny} {scheme}/{layout}/fp32: {mlups:.0f} MLUPS, {gbs:.0f} GB/s")
     return out
 
@@ -336,7 +342,8 @@ def d3q19_sweep(torch, lbm, workloads, log, steps=100, reps=5):
     # roofline of the fastest FP32 variant: its dominant kernels are HBM bound
     best = max((k for k in out["variants"] if k.endswith("/fp32")), key=lambda k: out["variants"][k]["mlups_median"])
     scheme, layout, _ = best.split("/")
-    kern = "k3_aa_even+k3_aa_odd" if scheme == "AA" else "k3_pull"
+    staged = layout == "collision"  # one update per launch
+    kern = ("k3_aa_even+k3_aa_odd" if scheme == "AA" else "k3_pull") if staged else "k3_fused"
     v = out["variants"][best]
     out["roofline"] = {"bound": "hbm", "variant": best, "achieved": v["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                        "frac": v["hbm_frac"], "bytes_per_node": 152,
@@ -425,8 +432,8 @@ def main():
         f"{value:.0f} MLUPS; diag status {st}, mass {diag[0]:.6f}")
 
     bpu = 72
-    launch_s = ev_ms * 1e-3 / args.steps
-    achieved = bpu * cells / launch_s / 1e9
+    update_s = ev_ms * 1e-3 / args.steps
+    achieved = bpu * cells / update_s / 1e9
     kernel_key = f"{kernel_name(scheme, layout, 'fp32', info['tile_x'])}/{layout}/fp32"
     traffic = stored_traffic(kernel_key)
     # practical peak: plain and non-temporal copies far beyond the caches
@@ -436,7 +443,7 @@ def main():
     working_set = info["device_bytes"]
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": kernel_key, "bytes_per_launch": bpu * cells, "avg_launch_us": round(launch_s * 1e6, 2),
+                "kernel": kernel_key, "bytes_per_update": bpu * cells, "update_us": round(update_s * 1e6, 2),
                 "working_set_mb": round(working_set / 2 ** 20, 1),
                 "cache_resident": working_set <= MALL_BYTES,
                 "copy_probe_gbs": round(copy_gbs, 1), "copy_probes": probes,
@@ -480,7 +487,7 @@ def main():
         roofline_offcache = {
             "bound": "hbm", "workload": hbm_ref["workload"], "variant": f"{scheme}/{layout}/fp32",
             "achieved": hv["algorithmic_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hv["frac_of_8tbs"],
-            "avg_launch_us": hv["avg_launch_us"], "frac_of_copy_probe": round(hv["algorithmic_gbs"] / copy_gbs, 4),
+            "update_us": hv["update_us"], "frac_of_copy_probe": round(hv["algorithmic_gbs"] / copy_gbs, 4),
             "best_variant": bk, "best_achieved": hbm_ref["variants"][bk]["algorithmic_gbs"],
             "best_frac": hbm_ref["variants"][bk]["frac_of_8tbs"],
             "best_frac_of_copy_probe": round(hbm_ref["variants"][bk]["algorithmic_gbs"] / copy_gbs, 4)}

@@ -254,9 +254,32 @@ int tile_threads(int scheme, int layout, int prec, int tx, int ty)
     return tx * ty;
 }
 
+// A one-lattice scheme gives its second lattice back, for other memory; single
+// updates in place from then on.
+bool give_back(lbm_ctx* c)
+{
+    if (is_two_lattice(c->grid.scheme) || !c->lat_raw[1]) return false;
+    if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
+    drop_graphs(c);
+    if (c->cur) {
+        std::swap(c->lat[0], c->lat[1]);
+        std::swap(c->lat_raw[0], c->lat_raw[1]);
+        c->cur = 0;
+    }
+    (void)hipFree(c->lat_raw[1]);
+    c->lat[1] = c->lat_raw[1] = nullptr;
+    c->bytes -= ((int64_t)c->lat_elems + 2 * c->guard) * c->elem;
+    c->plan = FusedPlan{};
+    return true;
+}
+
 lbm_status alloc(lbm_ctx* c, void** p, size_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (give_back(c)) e = hipMalloc(p, bytes);
+    }
     if (e != hipSuccess) {
         *p = nullptr;
         (void)hipGetLastError();
@@ -555,12 +578,6 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     const size_t raw_bytes = lat_bytes + 2 * (size_t)c->guard * c->elem;
     lbm_status st = alloc(c, &c->lat_raw[0], raw_bytes);
     if (st == LBM_OK && is_two_lattice(grid->scheme)) st = alloc(c, &c->lat_raw[1], raw_bytes);
-    if (st == LBM_OK && !is_two_lattice(grid->scheme) && raw_bytes <= SPARE_MOST && !is_neumann_inlet(bc->x_axis)) {
-        c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
-        if (c->plan.kk > 1 && alloc(c, &c->lat_raw[1], raw_bytes) != LBM_OK) c->plan = FusedPlan{};
-    }
-    for (int k = 0; k < 2; ++k)
-        if (c->lat_raw[k]) c->lat[k] = (char*)c->lat_raw[k] + (size_t)c->guard * c->elem;
     if (st == LBM_OK && c->edge_elems) st = alloc(c, &c->edge[0], (size_t)c->edge_elems * c->elem);
     if (st == LBM_OK && c->edge_elems) st = alloc(c, &c->edge[1], (size_t)c->edge_elems * c->elem);
     if (st == LBM_OK && grid->scheme == S_AA && is_inout(bc->x_axis))
@@ -573,6 +590,13 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
         dflags = nullptr;
         st = LBM_ENOMEM;
     }
+    // last: without memory for it every update is one in place
+    if (st == LBM_OK && !is_two_lattice(grid->scheme) && raw_bytes <= SPARE_MOST && !is_neumann_inlet(bc->x_axis)) {
+        c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
+        if (c->plan.kk > 1 && alloc(c, &c->lat_raw[1], raw_bytes) != LBM_OK) c->plan = FusedPlan{};
+    }
+    for (int k = 0; k < 2; ++k)
+        if (c->lat_raw[k]) c->lat[k] = (char*)c->lat_raw[k] + (size_t)c->guard * c->elem;
     if (st != LBM_OK) {
         free_all(c);
         delete c;

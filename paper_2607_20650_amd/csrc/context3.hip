@@ -98,14 +98,39 @@ lbm_status create3_error(lbm_status s, const std::string& msg)
     return s;
 }
 
+// What launches of several updates hold beside the state goes back, for other
+// memory; single updates from then on.
+bool give_back3(lbm3_ctx* c)
+{
+    if (!c->links || hipStreamSynchronize(c->stream) != hipSuccess) return false;
+    if (c->aa()) {
+        if (c->now) std::swap(c->lat[0], c->lat[1]);
+        c->now = 0;
+        (void)hipFree(c->lat[1]);
+        c->lat[1] = nullptr;
+    }
+    (void)hipFree(c->links);
+    c->links = nullptr;
+    c->kp.links = nullptr;
+    c->several = false;
+    return true;
+}
+
+bool alloc3(lbm3_ctx* c, void** p, size_t bytes)
+{
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    if (give_back3(c) && hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
 lbm_status ensure_readout3(lbm3_ctx* c)
 {
     if (c->readout) return LBM_OK;
-    if (hipMalloc((void**)&c->readout, (size_t)c->nodes() * Q3 * sizeof(float)) != hipSuccess) {
-        c->readout = nullptr;
-        (void)hipGetLastError();
+    if (!alloc3(c, (void**)&c->readout, (size_t)c->nodes() * Q3 * sizeof(float)))
         return c->fail(LBM_ENOMEM, "readout buffer allocation failed");
-    }
     return LBM_OK;
 }
 
@@ -349,8 +374,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
     // the push form is built from the pull form through a second lattice
     void* tmp = c->lat[c->now ^ 1];
     const bool borrow = c->state() == ST_PUSH && !tmp;
-    if (borrow && hipMalloc(&tmp, (size_t)c->lat_elems * c->elem) != hipSuccess) {
-        (void)hipGetLastError();
+    if (borrow && !alloc3(c, &tmp, (size_t)c->lat_elems * c->elem)) {
         return c->fail(LBM_ENOMEM, "temporary lattice for the state load");
     }
     hipError_t e = launch3_set_state(c->state(), c->grid.layout, c->grid.precision, c->kp, src, c->cur(), tmp,
@@ -372,13 +396,7 @@ lbm_status lbm3_diag(lbm3_ctx* c, double out[5])
     if (!c || !out) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     const Geometry3& g = c->kp.g;
-    auto get = [&](void** p, size_t bytes) {
-        if (*p) return true;
-        if (hipMalloc(p, bytes) == hipSuccess) return true;
-        *p = nullptr;
-        (void)hipGetLastError();
-        return false;
-    };
+    auto get = [&](void** p, size_t bytes) { return *p || alloc3(c, p, bytes); };
     if (!get((void**)&c->u_prev, (size_t)(3 * g.plane * g.nz) * sizeof(double)) ||
         !get((void**)&c->partials, (size_t)diag3_partials() * sizeof(double)) ||
         !get((void**)&c->dout, 8 * sizeof(double)))
