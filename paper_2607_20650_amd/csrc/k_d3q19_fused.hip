@@ -350,17 +350,20 @@ hipError_t launch3_links(const Geometry3& g, const uint8_t* types, uint32_t* lin
 bool fused3_serves(const Geometry3& g, int layout, int prec)
 {
     // Smaller grids leave most CUs without a block, and a block's planes come
-    // one after another.  Where a side is closed or has an inlet and an outlet,
-    // single updates look up the sources of whole walls: 100 x 60 x 80 FP32
-    // pull 32 against 20 us per update (FP16S-SR 27, 22), 64 x 64 x 64 the same
-    // either way (FP16S-SR 13, 20).  All periodic, they hold out while the
-    // lattices stay in the cache: 128 x 96 x 96 FP32 32 against 38 us, 100 x 200
-    // x 100 77 against 68.  The kernel's byte offsets within a plane stay below
-    // OFF_NONE.  The collision layout keeps its staged kernels: a wavefront's
-    // load of one direction is not one run there.
-    const bool walls = g.xa != AX_PERIODIC || g.ya != AX_PERIODIC || g.za != AX_PERIODIC;
+    // one after another.  Where the x axis is not periodic, two of a row's few
+    // wavefronts hold nodes whose sources single updates look up: 100 x 60 x 80
+    // duct FP32 pull 32 against 20 us per update, FP16S-SR 27 against 22, 64 x 64
+    // x 64 the same either way (FP16S-SR 13 against 20).  Elsewhere FP32 holds out
+    // while the lattices stay in the cache (128 x 96 x 96 32 against 38 us, 100 x
+    // 200 x 100 77 against 68), and 16-bit storage altogether: its codec makes two
+    // updates per launch bound by instructions (256^3 FP16S 250 against 322 us).
+    // The kernel's byte offsets within a plane stay below OFF_NONE.  The
+    // collision layout keeps its staged kernels: a wavefront's load of one
+    // direction is not one run there.
+    const bool sides = g.xa != AX_PERIODIC;
+    if (prec != P_FP32 && !sides) return false;
     const int64_t plane = (layout == L_BLOCKED ? g.pstep : g.plane) * (prec == P_FP32 ? 4 : 2);
-    return layout != L_COLLISION && g.nx * g.ny * g.nz >= (walls ? 320000 : 1500000) && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
+    return layout != L_COLLISION && g.nx * g.ny * g.nz >= (sides ? 320000 : 1500000) && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
            plane < ((int64_t)1 << 30) && g.plane < ((int64_t)1 << 28);
 }
 

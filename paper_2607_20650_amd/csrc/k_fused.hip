@@ -244,13 +244,20 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // so short that the rows recomputed for eight cost more than two launches
     // less (6000 x 400 bundle: 10.6 against 11.2 us per update, alone 14.4
     // against 17.6; 1000 x 2600: 12.8, 13.5; 4096 x 1024: 17.3, 16.7).
-    const int most = prec != P_FP32 ? fused_most<uint16_t>() : g.nx * g.ny <= 3000000 ? 6 : fused_most<float>();
+    // The FP16S-SR pull spends most on its codec: three, on 1280 blocks (4096 x
+    // 1024 alone 29.6 against 31.6 us, beside two others 22.4 against 22.0;
+    // single updates, which run in the 256 MB cache alone, 27 and 43).
+    const bool push = scheme == S_PUSH || scheme == S_AA, sr = prec == P_FP16SR && !push;
+    const int most = sr                ? 3
+                     : prec != P_FP32  ? fused_most<uint16_t>()
+                     : g.nx * g.ny <= 3000000 ? 6
+                                              : fused_most<float>();
     q.kk = (int)std::min<int64_t>(most, g.ny);
     if (scheme == S_AA) q.kk &= ~1;
     if (q.kk < 2) return FusedPlan{};
-    const bool push = scheme == S_PUSH || scheme == S_AA;
+    const int64_t resident = sr ? 1280 : (push && prec == P_FP32 ? 768 : 1024);
     const int64_t w = (int64_t)(64 - 2 * q.kk) * FUSED_WAVES, cols = (g.nx + w - 1) / w;
-    const int64_t chunks = std::max<int64_t>((push && prec == P_FP32 ? 768 : 1024) / cols, 1);
+    const int64_t chunks = std::max<int64_t>(resident / cols, 1);
     const int64_t rows = (g.ny + chunks - 1) / chunks;
     q.rows = (int)std::min<int64_t>(std::max<int64_t>(rows, 12), 128);
     return q;
