@@ -4,8 +4,10 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <thread>
+#include <vector>
 
 #include "lbm.h"
 #include "lbm_common.hpp"
@@ -59,34 +61,94 @@ inline bool all_finite(const float* v, int64_t n)
     return !bad;
 }
 
+// Pinned buffers for HostRing, shared by the simulations of the process: a
+// call takes one and returns it; two at most wait for the next, and all are
+// freed with the last simulation that used them.  (One of its own per
+// simulation cost each first readout 2 ms: the processor's first touch of 8
+// MiB of pinned memory.)
+class PinnedPool {
+public:
+    static constexpr size_t BYTES = (size_t)8 << 20;
+    void join()
+    {
+        const std::lock_guard<std::mutex> lock(mu_);
+        ++users_;
+    }
+    void leave()
+    {
+        const std::lock_guard<std::mutex> lock(mu_);
+        if (--users_ > 0) return;
+        for (char* b : free_) (void)hipHostFree(b);
+        free_.clear();
+    }
+    char* take()
+    {
+        {
+            const std::lock_guard<std::mutex> lock(mu_);
+            if (!free_.empty()) {
+                char* const b = free_.back();
+                free_.pop_back();
+                return b;
+            }
+        }
+        char* b = nullptr;
+        if (hipHostMalloc((void**)&b, BYTES, hipHostMallocPortable) == hipSuccess) return b;
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    void give(char* b)
+    {
+        {
+            const std::lock_guard<std::mutex> lock(mu_);
+            if (free_.size() < 2) {
+                free_.push_back(b); // capacity reserved: does not throw
+                return;
+            }
+        }
+        (void)hipHostFree(b);
+    }
+    static PinnedPool& get()
+    {
+        static PinnedPool* const p = new PinnedPool(); // outlives every simulation
+        return *p;
+    }
+
+private:
+    PinnedPool() { free_.reserve(2); }
+    std::mutex mu_;
+    std::vector<char*> free_;
+    int users_ = 0;
+};
+
 // Copies from the device to pageable host memory through pinned chunks, the
 // host's copy of one beside the transfer of the next, in two segments by two
 // threads.  The runtime's own pageable copy takes 1200 us for 21.6 MB (18 GB/s)
 // where the transfer to pinned memory takes 385; here 680 (one thread 825: it
 // reads what the transfer left in memory; three and more the same as two), and
-// into memory not touched before 1100 instead of 2200 (one thread).  The
-// runtime's copies to the device (580 us) did not gain this way.  One ring per
-// simulation, 8 MiB from its first large copy on.  Pinned and device memory,
-// and copies too small to gain, go straight to the runtime.
+// into memory not touched before 1400 instead of 2200.  The runtime's copies
+// to the device (580 us) did not gain this way.  Pinned and device memory, and
+// copies too small to gain, go straight to the runtime.
 class HostRing {
 public:
     // src (device) -> dst; on return the data is in dst, or the copy is
     // enqueued on s
     hipError_t to_host(void* dst, const void* src, size_t bytes, hipStream_t s)
     {
-        if (!serves(dst, bytes)) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
-        return segments(bytes, [=](int w, size_t lo, size_t hi) {
+        char* const buf = serves(dst, bytes) ? PinnedPool::get().take() : nullptr;
+        if (!buf) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+        const hipError_t res = segments(bytes, [=](int w, size_t lo, size_t hi) {
             const size_t chunk = chunk_of(hi - lo), n = (hi - lo + chunk - 1) / chunk;
             for (size_t i = 0; i < n + SLOTS; ++i) {
+                char* const slot = buf + (w * SLOTS + i % SLOTS) * CHUNK;
                 if (i >= SLOTS && i - SLOTS < n) { // the chunk sent for before in this slot
                     const size_t at = lo + (i - SLOTS) * chunk;
                     const hipError_t e = hipEventSynchronize(ev_[w][i % SLOTS]);
                     if (e != hipSuccess) return e;
-                    std::memcpy((char*)dst + at, slot(w, i), std::min(chunk, hi - at));
+                    std::memcpy((char*)dst + at, slot, std::min(chunk, hi - at));
                 }
                 if (i < n) {
                     const size_t at = lo + i * chunk;
-                    hipError_t e = hipMemcpyAsync(slot(w, i), (const char*)src + at, std::min(chunk, hi - at),
+                    hipError_t e = hipMemcpyAsync(slot, (const char*)src + at, std::min(chunk, hi - at),
                                                   hipMemcpyDeviceToHost, s);
                     if (e == hipSuccess) e = hipEventRecord(ev_[w][i % SLOTS], s);
                     if (e != hipSuccess) return e;
@@ -94,6 +156,9 @@ public:
             }
             return hipSuccess;
         });
+        if (res != hipSuccess) (void)hipStreamSynchronize(s); // nothing writes the buffer any more
+        PinnedPool::get().give(buf);
+        return res;
     }
     void release()
     {
@@ -102,13 +167,13 @@ public:
                 if (e) (void)hipEventDestroy(e);
                 e = nullptr;
             }
-        if (buf_) (void)hipHostFree(buf_);
-        buf_ = nullptr;
+        if (ready_) PinnedPool::get().leave();
+        ready_ = false;
     }
 
 private:
     static constexpr size_t CHUNK = (size_t)2 << 20, SLOTS = 2, LEAST = (size_t)1 << 20, WORKERS = 2;
-    char* slot(int w, size_t i) const { return buf_ + (w * SLOTS + i % SLOTS) * CHUNK; }
+    static_assert(CHUNK * SLOTS * WORKERS <= PinnedPool::BYTES, "slots of all workers");
     // a few chunks per segment, in whole pages: enough to overlap, few enough
     // that the 10 us each takes the host to enqueue do not count
     static size_t chunk_of(size_t bytes)
@@ -152,21 +217,23 @@ private:
         } else {
             (void)hipGetLastError(); // memory that the runtime does not know
         }
-        if (buf_) return true;
-        bool ok = hipHostMalloc((void**)&buf_, WORKERS * SLOTS * CHUNK, hipHostMallocDefault) == hipSuccess;
-        if (!ok) buf_ = nullptr;
+        if (ready_) return true;
+        bool ok = true;
         for (auto& w : ev_)
             for (hipEvent_t& e : w) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
-        if (!ok) {
+        if (ok) {
+            PinnedPool::get().join();
+            ready_ = true;
+        } else {
             (void)hipGetLastError();
             release();
             off_ = true;
         }
         return ok;
     }
-    char* buf_ = nullptr;
     hipEvent_t ev_[WORKERS][SLOTS] = {};
-    bool off_ = false; // no pinned memory: the runtime's copies
+    bool ready_ = false;
+    bool off_ = false; // no events: the runtime's copies
 };
 
 } // namespace lbm
