@@ -232,9 +232,11 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
         return q;
     }
     // FP16C on lattices that fit the 256 MB cache is bound by its codec either
-    // way and loses to the recomputed nodes (4096 x 1024: 31 against 28 us per
-    // update, FP16C-SR 36 against 31).
-    if ((prec == P_FP16C || prec == P_FP16CSR) && 18 * g.P * elem <= ((int64_t)256 << 20)) return q;
+    // way and loses to the recomputed nodes where the scheme's own kernel is one
+    // of the fast ones (4096 x 1024, FP16C / FP16C-SR: 32 / 36 us per update here;
+    // NPTL 28 - 34 / 30 - 34, AA and PUSH stream 33 / 35 us; the others 39 - 62).
+    const bool fast = scheme == S_NPTL || ((scheme == S_AA || scheme == S_PUSH) && layout == L_STREAM);
+    if ((prec == P_FP16C || prec == P_FP16CSR) && fast && 18 * g.P * elem <= ((int64_t)256 << 20)) return q;
     // Strips: chunks of rows that make at most 1024 blocks, four per CU, all
     // resident at once: one round, few recomputed rows at the chunks' ends
     // (4096 x 1024 FP32: 21.4 us per update; 768 blocks 23.0, 512 27.2, 1280
