@@ -441,7 +441,7 @@ def main():
               for m in ("copy", "copy_nt") for sz in (1, 4)}
     copy_gbs = max(probes.values())
     working_set = info["device_bytes"]
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    roofline = {"bound": "valu" if "k_fused" in kernel_key else "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "kernel": kernel_key, "bytes_per_update": bpu * cells, "update_us": round(update_s * 1e6, 2),
                 "working_set_mb": round(working_set / 2 ** 20, 1),
