@@ -381,31 +381,16 @@ hipError_t launch_macros(int state, int layout, int prec, const KParams& p, cons
 
 // ---------------------------------------------------------------- FP64 diagnostics
 constexpr int DIAG_BLOCKS = 1024;
-constexpr int DIAG_THREADS = 256;
+constexpr int DIAG_THREADS = 256; // as block_sums takes them
 constexpr int DIAG_VALUES = 5;
 
 int diag_partials() { return DIAG_BLOCKS * DIAG_VALUES; }
-
-// Fixed-shape block reduction (deterministic order).
-__device__ __forceinline__ double block_sum(double v, double* sh)
-{
-    const int tid = threadIdx.x;
-    sh[tid] = v;
-    __syncthreads();
-    for (int w = DIAG_THREADS / 2; w > 0; w >>= 1) {
-        if (tid < w) sh[tid] += sh[tid + w];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
 
 template <int S, int L, class T>
 __global__ void __launch_bounds__(DIAG_THREADS)
     k_diag(KParams p, const T* __restrict__ lat, double* __restrict__ u_prev, int have_prev, double* __restrict__ part)
 {
-    __shared__ double sh[DIAG_THREADS];
+    __shared__ double sh[DIAG_VALUES * DIAG_THREADS];
     const int64_t N = p.g.nx * p.g.ny;
     double acc[DIAG_VALUES] = {0, 0, 0, 0, 0};
     for (int64_t m = (int64_t)blockIdx.x * DIAG_THREADS + threadIdx.x; m < N; m += (int64_t)DIAG_BLOCKS * DIAG_THREADS) {
@@ -440,21 +425,19 @@ __global__ void __launch_bounds__(DIAG_THREADS)
         }
         acc[4] += ux * ux + uy * uy;
     }
-    for (int k = 0; k < DIAG_VALUES; ++k) {
-        const double t = block_sum(acc[k], sh);
-        if (threadIdx.x == 0) part[blockIdx.x * DIAG_VALUES + k] = t;
-    }
+    block_sums(acc, sh, part + blockIdx.x * DIAG_VALUES);
 }
 
 __global__ void __launch_bounds__(DIAG_THREADS) k_diag_final(const double* __restrict__ part, double* __restrict__ out)
 {
-    __shared__ double sh[DIAG_THREADS];
-    for (int k = 0; k < DIAG_VALUES; ++k) {
-        double a = 0.0;
-        for (int b = threadIdx.x; b < DIAG_BLOCKS; b += DIAG_THREADS) a += part[b * DIAG_VALUES + k];
-        const double t = block_sum(a, sh);
-        if (threadIdx.x == 0) out[k] = t;
+    __shared__ double sh[DIAG_VALUES * DIAG_THREADS];
+    double acc[DIAG_VALUES] = {};
+#pragma unroll
+    for (int b = threadIdx.x; b < DIAG_BLOCKS; b += DIAG_THREADS) {
+#pragma unroll
+        for (int k = 0; k < DIAG_VALUES; ++k) acc[k] += part[b * DIAG_VALUES + k];
     }
+    block_sums(acc, sh, out);
 }
 
 // The four diagnostics from the five sums of k_diag_final: mass, momentum,

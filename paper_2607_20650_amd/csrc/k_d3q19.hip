@@ -999,22 +999,8 @@ __global__ void k3_macros(KParams3 p, const T* __restrict__ lat, float* __restri
 // FP64 mass, momentum (3) and the residual terms of the velocity change,
 // summed per block in a fixed order, then over blocks (deterministic).
 constexpr int DIAG3_BLOCKS = 1024;
-constexpr int DIAG3_THREADS = 256;
+constexpr int DIAG3_THREADS = 256; // as block_sums takes them
 constexpr int DIAG3_VALUES = 6;
-
-__device__ __forceinline__ double block_sum3(double v, double* sh)
-{
-    const int tid = threadIdx.x;
-    sh[tid] = v;
-    __syncthreads();
-    for (int w = DIAG3_THREADS / 2; w > 0; w >>= 1) {
-        if (tid < w) sh[tid] += sh[tid + w];
-        __syncthreads();
-    }
-    const double r = sh[0];
-    __syncthreads();
-    return r;
-}
 
 // part[block][k]: k = 0 mass, 1..3 momentum, 4 sum |u - u_prev|^2, 5 sum |u|^2;
 // u_prev (3 doubles per padded node) is read when have_prev and overwritten.
@@ -1022,7 +1008,7 @@ template <int S, int L, class T>
 __global__ void __launch_bounds__(DIAG3_THREADS)
     k3_diag(KParams3 p, const T* __restrict__ lat, double* __restrict__ u_prev, int have_prev, double* __restrict__ part)
 {
-    __shared__ double sh[DIAG3_THREADS];
+    __shared__ double sh[DIAG3_VALUES * DIAG3_THREADS];
     const int64_t N = p.g.nx * p.g.ny * p.g.nz;
     double acc[DIAG3_VALUES] = {0, 0, 0, 0, 0, 0};
     for (int64_t m = (int64_t)blockIdx.x * DIAG3_THREADS + threadIdx.x; m < N;
@@ -1055,21 +1041,19 @@ __global__ void __launch_bounds__(DIAG3_THREADS)
         acc[4] += du;
         acc[5] += uu;
     }
-    for (int k = 0; k < DIAG3_VALUES; ++k) {
-        const double t = block_sum3(acc[k], sh);
-        if (threadIdx.x == 0) part[blockIdx.x * DIAG3_VALUES + k] = t;
-    }
+    block_sums(acc, sh, part + blockIdx.x * DIAG3_VALUES);
 }
 
 __global__ void __launch_bounds__(DIAG3_THREADS) k3_diag_final(const double* __restrict__ part, double* __restrict__ out)
 {
-    __shared__ double sh[DIAG3_THREADS];
-    for (int k = 0; k < DIAG3_VALUES; ++k) {
-        double a = 0.0;
-        for (int b = threadIdx.x; b < DIAG3_BLOCKS; b += DIAG3_THREADS) a += part[b * DIAG3_VALUES + k];
-        const double t = block_sum3(a, sh);
-        if (threadIdx.x == 0) out[k] = t;
+    __shared__ double sh[DIAG3_VALUES * DIAG3_THREADS];
+    double acc[DIAG3_VALUES] = {};
+#pragma unroll
+    for (int b = threadIdx.x; b < DIAG3_BLOCKS; b += DIAG3_THREADS) {
+#pragma unroll
+        for (int k = 0; k < DIAG3_VALUES; ++k) acc[k] += part[b * DIAG3_VALUES + k];
     }
+    block_sums(acc, sh, out);
 }
 
 int diag3_partials() { return DIAG3_BLOCKS * DIAG3_VALUES; }
