@@ -240,8 +240,9 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // Strips: chunks of rows that make at most 1024 blocks, four per CU, all
     // resident at once: one round, few recomputed rows at the chunks' ends
     // (4096 x 1024 FP32: 21.4 us per update; 768 blocks 23.0, 512 27.2, 1280
-    // 24.1); at most 128 rows.  Of the FP32 push form three per CU are resident
-    // (the same grid: 768 blocks 24.8, 1024 26.5).
+    // 24.1); whole rounds more where that leaves more than 128 rows (8192 x 4096
+    // alone: two rounds 135 us, 1.3 146).  Of the FP32 push form three per CU
+    // are resident (4096 x 1024: 768 blocks 24.8, 1024 26.5).
     // FP32 up to 3 million nodes: six updates per launch, where the chunks are
     // so short that the rows recomputed for eight cost more than two launches
     // less (6000 x 400 bundle: 10.6 against 11.2 us per update, alone 14.4
@@ -259,9 +260,12 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     if (q.kk < 2) return FusedPlan{};
     const int64_t resident = sr ? 1280 : (push && prec == P_FP32 ? 768 : 1024);
     const int64_t w = (int64_t)(64 - 2 * q.kk) * FUSED_WAVES, cols = (g.nx + w - 1) / w;
-    const int64_t chunks = std::max<int64_t>(resident / cols, 1);
-    const int64_t rows = (g.ny + chunks - 1) / chunks;
-    q.rows = (int)std::min<int64_t>(std::max<int64_t>(rows, 12), 128);
+    int64_t rows = INT64_MAX;
+    for (int64_t rounds = 1; rows > 128; ++rounds) {
+        const int64_t chunks = std::max<int64_t>(resident * rounds / cols, 1);
+        rows = (g.ny + chunks - 1) / chunks;
+    }
+    q.rows = (int)std::max<int64_t>(rows, 12);
     return q;
 }
 
