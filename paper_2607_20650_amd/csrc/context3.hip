@@ -42,7 +42,7 @@ struct lbm3_ctx {
     void* lat[2] = {nullptr, nullptr};
     void* obuf = nullptr; // AA with an outlet: 5 values per (y, z) row
     uint8_t* types = nullptr;
-    uint32_t* links = nullptr; // link words, where launches do several updates
+    uint32_t* links = nullptr; // link words, if there was memory for them
     float* readout = nullptr; // 19 * N floats, lazily
     double* u_prev = nullptr; // 3 * padded nodes, lazily (diagnostics)
     double* partials = nullptr;
@@ -253,21 +253,22 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
         return create3_error(LBM_ENOMEM, "device memory exhausted");
     }
     c->kp.types = c->types;
-    // several updates per launch need link words and, for AA, a second lattice;
-    // without memory for them every update is a launch of its own
-    if (fused3_serves(g, grid->layout, grid->precision) && (grid->scheme != LBM_AA || lat_bytes <= SPARE_MOST)) {
-        bool extra = hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) == hipSuccess;
-        if (!extra) c->links = nullptr;
-        if (extra && grid->scheme == LBM_AA && hipMalloc(&c->lat[1], lat_bytes) != hipSuccess) {
+    // optional: link words (without them boundary nodes look up their
+    // neighbours' types) and, for several updates per launch of AA, a second
+    // lattice
+    if (grid->layout != LBM_COLLISION && hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) != hipSuccess) {
+        c->links = nullptr;
+        (void)hipGetLastError();
+    }
+    c->several = c->links && fused3_serves(g, grid->layout, grid->precision);
+    if (c->several && grid->scheme == LBM_AA) {
+        c->several = lat_bytes <= SPARE_MOST && hipMalloc(&c->lat[1], lat_bytes) == hipSuccess;
+        if (!c->several) {
             c->lat[1] = nullptr;
-            (void)hipFree(c->links);
-            c->links = nullptr;
-            extra = false;
+            (void)hipGetLastError();
         }
-        if (!extra) (void)hipGetLastError();
     }
     c->kp.links = c->links;
-    c->several = c->links != nullptr;
     hipError_t e = hipMemcpyAsync(dflags, flags, (size_t)N, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = launch3_types(g, dflags, c->types, c->stream);
     if (e == hipSuccess && c->links) e = launch3_links(g, c->types, c->links, c->stream);

@@ -54,7 +54,7 @@ struct KParams3 {
     Geometry3 g;
     Physics3 ph;
     const uint8_t* types; // [nz][ny][px]; padding columns are solid
-    const uint32_t* links; // link words [nz][ny][px] (k3_links), or null: single updates only
+    const uint32_t* links; // link words [nz][ny][px] (k3_links), or null
 };
 
 // Whether the collision layout runs the LDS-staged kernels: 64 x ty tiles
