@@ -16,9 +16,9 @@
 //
 // Two nodes per thread and 8 wavefronts per CU (226 registers): one node per
 // thread and 16 wavefronts need more than the 128 registers they may have.
-// Per update, three simulations in turn: 201 x 97 x 85 AA FP32 stream 104 us
-// in place one by one, 55 us here; 230 x 140 x 200 FP16S stream pull 302 and
-// 125 us; 256^3 FP32 blocked pull 520 and 445 us (alone 512 and 402), where a
+// Per update, three simulations in turn: 201 x 97 x 85 AA FP32 stream 66 us
+// in place one by one, 54 us here; 230 x 140 x 200 FP32 stream pull 257 and
+// 184 us; 256^3 FP32 blocked pull 520 and 445 us (alone 512 and 402), where a
 // block's plane takes 6 us: 4 us of VALU work (a fifth of it on columns past
 // the grid, 256 being 4.3 times 60), the rest exposed loads and stores.  Stores of four columns gathered through LDS (10 instead of 38
 // per plane) lost 20 %.
@@ -349,21 +349,23 @@ hipError_t launch3_links(const Geometry3& g, const uint8_t* types, uint32_t* lin
 
 bool fused3_serves(const Geometry3& g, int layout, int prec)
 {
-    // Smaller grids leave most CUs without a block, and a block's planes come
-    // one after another.  Where the x axis is not periodic, two of a row's few
-    // wavefronts hold nodes whose sources single updates look up: 100 x 60 x 80
-    // duct FP32 pull 32 against 20 us per update, FP16S-SR 27 against 22, 64 x 64
-    // x 64 the same either way (FP16S-SR 13 against 20).  Elsewhere FP32 holds out
-    // while the lattices stay in the cache (128 x 96 x 96 32 against 38 us, 100 x
-    // 200 x 100 77 against 68), and 16-bit storage altogether: its codec makes two
-    // updates per launch bound by instructions (256^3 FP16S 250 against 322 us).
-    // The kernel's byte offsets within a plane stay below OFF_NONE.  The
-    // collision layout keeps its staged kernels: a wavefront's load of one
-    // direction is not one run there.
-    const bool sides = g.xa != AX_PERIODIC;
-    if (prec != P_FP32 && !sides) return false;
+    // While the lattices stay in the cache, single updates hold out: a block's
+    // planes come one after another, and small grids leave CUs without a block
+    // (per update with two simulations beside / alone, FP32 pull: 128 x 96 x 96
+    // duct 41 / 41 us against 37 / 39 here, 100 x 60 x 80 18 / 24, 18 / 23; 201 x
+    // 97 x 85 65 / 64, 49 / 51).  16-bit storage makes two updates per launch
+    // bound by its codec: it gains where the x axis is not periodic, so that two
+    // of a row's few wavefronts hold boundary nodes in single updates, from 2
+    // million nodes on (FP16S, AA: 160 x 130 x 128 86 / 73 against 61 / 70), the
+    // costlier formats from 4 (FP16S-SR pull: 160 x 130 x 128 70 / 64 against 74 /
+    // 82, 230 x 140 x 200 181 / 181 against 143 / 156); 256^3 all periodic FP16S
+    // 258 against 322 alone.  The kernel's byte offsets within a plane stay below
+    // OFF_NONE.  The collision layout keeps its staged kernels: a wavefront's
+    // load of one direction is not one run there.
+    if (prec != P_FP32 && g.xa == AX_PERIODIC) return false;
+    const int64_t least = prec == P_FP32 ? 1500000 : prec == P_FP16S ? 2000000 : 4000000;
     const int64_t plane = (layout == L_BLOCKED ? g.pstep : g.plane) * (prec == P_FP32 ? 4 : 2);
-    return layout != L_COLLISION && g.nx * g.ny * g.nz >= (sides ? 320000 : 1500000) && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
+    return layout != L_COLLISION && g.nx * g.ny * g.nz >= least && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
            plane < ((int64_t)1 << 30) && g.plane < ((int64_t)1 << 28);
 }
 

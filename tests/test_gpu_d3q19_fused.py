@@ -18,21 +18,14 @@ P, C, IO = o3.PERIODIC, o3.CLOSED, o3.INFLOW_OUTFLOW
 AXES = [(C, C, C), (IO, C, P), (IO, P, C), (P, C, P), (P, P, P)]
 
 
-@pytest.mark.parametrize("precision", ALL_PRECISIONS)
-@pytest.mark.parametrize("nx,ny,nz", [(70, 67, 71), (5, 260, 260), (2, 400, 420), (323, 1000, 1), (130, 25, 101),
-                                      (420, 400, 2), (1, 600, 600), (60, 73, 74)])
-def test_two_updates_per_launch_bitwise(nx, ny, nz, precision):
+def _compare(nx, ny, nz, precision, all_axes, variants):
     from paper_2607_20650_amd.lbm import Simulation3
-    for k, axes in enumerate(AXES):
+    flags = W.random_flags3(nx, ny, nz, 0.1, nx + ny)
+    st = W.random_state3(nx, ny, nz, 0.02, seed=5, dtype=np.float32)
+    for k, axes in enumerate(all_axes):
         if axes[0] == IO and nx < 2:
             continue
-        if axes[0] == P:  # FP32, from 1.5 million nodes on
-            if nx < 60 or ny > 80:
-                continue
-            nz = nz * 5
-        flags = W.random_flags3(nx, ny, nz, 0.1, nx + ny)
-        st = W.random_state3(nx, ny, nz, 0.02, seed=5, dtype=np.float32)
-        for scheme, layout in [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "blocked" if k % 2 else "stream")]:
+        for scheme, layout in variants(k):
             out = []
             for calls in ([1] * 7, [1, 2, 4]):
                 with Simulation3(flags, 0.8, *axes, u_in=(0.05, 0.01, -0.01), g=(1e-4, 2e-4, -1e-4),
@@ -47,13 +40,28 @@ def test_two_updates_per_launch_bitwise(nx, ny, nz, precision):
             assert np.array_equal(a, b, equal_nan=True), (axes, scheme, layout, np.argwhere(a != b)[:3])
 
 
+# from 1.5 million nodes on
+@pytest.mark.parametrize("nx,ny,nz", [(70, 67, 330), (5, 560, 560), (2, 900, 900), (1300, 1200, 1), (130, 125, 95),
+                                      (900, 900, 2), (1, 1250, 1250), (60, 73, 345)])
+def test_two_updates_per_launch_bitwise(nx, ny, nz):
+    _compare(nx, ny, nz, "fp32", AXES,
+             lambda k: [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "blocked" if k % 2 else "stream")])
+
+
+# from 4 million nodes on, x axis not periodic
+@pytest.mark.parametrize("precision", [p for p in ALL_PRECISIONS if p != "fp32"])
+def test_two_updates_per_launch_bitwise_16_bit(precision):
+    _compare(131, 126, 250, precision, AXES[:2],
+             lambda k: [("NPTL", "blocked" if k else "stream"), ("AA", "stream" if k else "blocked")])
+
+
 @pytest.mark.parametrize("scheme", ["NPTL", "AA"])
 def test_captured_steps_replay_3d(scheme):
     """As for the 2-D schemes: a captured even number of updates can be
     replayed between eager ones."""
     import torch
     from paper_2607_20650_amd.lbm import Simulation3
-    flags = W.random_flags3(130, 50, 60, 0.1, 4)
+    flags = W.random_flags3(130, 100, 120, 0.1, 4)
     kw = dict(u_in=(0.05, 0.01, 0.0), u0=(0.02, 0.0, 0.0), scheme=scheme)
     with Simulation3(flags, 0.8, IO, C, C, **kw) as sim, Simulation3(flags, 0.8, IO, C, C, **kw) as ref:
         sim.step(6)
