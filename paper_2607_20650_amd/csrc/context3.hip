@@ -256,7 +256,8 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
     // optional: link words (without them boundary nodes look up their
     // neighbours' types) and, for several updates per launch of AA, a second
     // lattice
-    if (grid->layout != LBM_COLLISION && hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) != hipSuccess) {
+    if (grid->layout != LBM_COLLISION &&
+        hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) != hipSuccess) {
         c->links = nullptr;
         (void)hipGetLastError();
     }

@@ -344,7 +344,10 @@ __device__ __forceinline__ void aa_odd_regular(const KParams3& p, T* lat, const 
 }
 
 // (-1, -c_y, -c_z) of the directions with c_x = -1.
-__host__ __device__ constexpr int q3_mirror(int i) { return i == 1 ? 15 : (i == 15 ? 1 : (i == 5 ? 11 : (i == 11 ? 5 : i))); }
+__host__ __device__ constexpr int q3_mirror(int i)
+{
+    return i == 1 ? 15 : (i == 15 ? 1 : (i == 5 ? 11 : (i == 11 ? 5 : i)));
+}
 
 // Odd AA update of an irregular node: the boundary rules, loads and stores
 // direct.

@@ -20,8 +20,8 @@
 // in place one by one, 54 us here; 230 x 140 x 200 FP32 stream pull 257 and
 // 184 us; 256^3 FP32 blocked pull 520 and 445 us (alone 512 and 402), where a
 // block's plane takes 6 us: 4 us of VALU work (a fifth of it on columns past
-// the grid, 256 being 4.3 times 60), the rest exposed loads and stores.  Stores of four columns gathered through LDS (10 instead of 38
-// per plane) lost 20 %.
+// the grid, 256 being 4.3 times 60), the rest exposed loads and stores.  Stores
+// of four columns gathered through LDS (10 instead of 38 per plane) lost 20 %.
 #include <algorithm>
 
 #include "lbm3_device.hpp"
