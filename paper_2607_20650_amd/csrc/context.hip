@@ -81,7 +81,7 @@ struct lbm_ctx {
     int cur = 0;    // the lattice that holds the state
     bool edges_old = false; // one-lattice tiled schemes: edge[] is not that of the state
     FusedPlan plan; // several updates per launch
-    bool direct = false; // no graphs: calls have been captured
+    bool captured = false; // calls have been captured
     int32_t bundle = 32;
     int32_t block = 256;
     hipGraph_t graph[4] = {}; // by graph_key
@@ -368,6 +368,19 @@ lbm_status build_graph(lbm_ctx* c, int key)
     return LBM_OK;
 }
 
+// Before a call that records the address of a lattice: a captured one is
+// replayed with the lattices it was captured with, so from the first one on
+// the context does single updates, which leave the state where they found it
+// after every even number, and bundles by direct launch.  (Several updates per
+// launch leave it in either lattice, by the number of launches: a readout
+// captured before 100 updates of AA, in 13 launches, would read the other one.)
+void watch_capture(lbm_ctx* c)
+{
+    if (c->plan.kk == 1 || !capturing(c->stream)) return;
+    c->captured = true;
+    c->plan = FusedPlan{};
+}
+
 lbm_status ensure_readout(lbm_ctx* c)
 {
     if (c->readout) return LBM_OK;
@@ -637,13 +650,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    // A captured call is replayed on the lattice it was captured with, so from
-    // the first one on the context does single updates, which leave the state
-    // where they found it after every even number, and bundles by direct launch.
-    if (c->plan.kk > 1 && capturing(c->stream)) {
-        c->plan = FusedPlan{};
-        c->direct = true;
-    }
+    watch_capture(c);
     const int most = c->bundle > 0 ? c->plan.kk : 1;
     if (n > 0 && c->edge_elems && most > 1) c->edges_old = true;
     if (n > 0 && c->edges_old && most == 1) {
@@ -656,7 +663,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     // updates as 6 graphs of 3 launches and one more 207 us, as 17 launches
     // 171; graphs of 8 launches save up to 40 % beside other simulations (513 x
     // 257, 96 updates: 100 against 117 - 142 us).
-    const bool graphs = !c->direct && c->bundle > 4 * (int64_t)most;
+    const bool graphs = !c->captured && c->bundle > 4 * (int64_t)most;
     while (graphs && n >= c->bundle) {
         const int key = graph_key(c);
         if (!c->gexec[key]) {
@@ -702,6 +709,7 @@ lbm_status lbm_macros(lbm_ctx* c, float* rho, float* u, int on_device)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (!rho && !u) return LBM_OK;
+    watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     if (on_device) {
         return c->check(launch_macros(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), rho, u,
@@ -723,6 +731,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
+    watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     if (on_device)
         return c->check(launch_get_populations(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), f,
@@ -741,6 +750,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
+    watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     const float* src = f;
     if (!on_device) {
@@ -824,6 +834,7 @@ lbm_status lbm_diag_noalloc(lbm_ctx* c, double* u_prev, int32_t have_prev, doubl
     double* scr = nullptr;
     lbm_status st = noalloc_scratch(c, &scr);
     if (st != LBM_OK) return st;
+    watch_capture(c);
     double* sums = scr + diag_partials(); // 5 sums after the partials
     hipError_t e = launch_diag(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), u_prev,
                                have_prev ? 1 : 0, scr, sums, c->stream);

@@ -126,6 +126,15 @@ bool alloc3(lbm3_ctx* c, void** p, size_t bytes)
     return false;
 }
 
+// Before a call that records the address of a lattice: a captured one is
+// replayed with the lattices it was captured with, so from the first one on
+// the context does single updates, which leave the state where they found it
+// after every even number.
+void watch_capture3(lbm3_ctx* c)
+{
+    if (c->several && capturing(c->stream)) c->several = false;
+}
+
 lbm_status ensure_readout3(lbm3_ctx* c)
 {
     if (c->readout) return LBM_OK;
@@ -293,10 +302,7 @@ lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    // a captured call is replayed on the lattice it was captured with: from the
-    // first one on single updates, which leave the state where they found it
-    // after every even number
-    if (c->several && capturing(c->stream)) c->several = false;
+    watch_capture3(c);
     while (n > 0) {
         const int parity = (int)(c->t & 1);
         void* const src = c->lat[c->now];
@@ -326,6 +332,7 @@ lbm_status lbm3_macros(lbm3_ctx* c, float* rho, float* u, int on_device)
 {
     if (!c) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
+    watch_capture3(c);
     if (on_device)
         return c->check(launch3_macros(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(), rho, u,
                                        c->stream),
@@ -346,6 +353,7 @@ lbm_status lbm3_get_populations(lbm3_ctx* c, float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
+    watch_capture3(c);
     if (on_device)
         return c->check(launch3_get_populations(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(), f,
                                                 c->stream),
@@ -364,6 +372,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
     if (c->poisoned) return LBM_EDEVICE;
+    watch_capture3(c);
     const float* src = f;
     if (!on_device) {
         lbm_status st = ensure_readout3(c);

@@ -38,7 +38,9 @@ int64_t count_updated(const lbm_grid* grid, const uint8_t* flags, const lbm_bc* 
 inline bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
+    (void)hipGetLastError();
+    return false;
 }
 
 // Whether any flag is neither 0 nor 1.  No early exit, so that it vectorises.

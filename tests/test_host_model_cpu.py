@@ -1,0 +1,34 @@
+"""Host code of the simulation contexts on a modelled device.
+
+``csrc/context.hip`` and ``csrc/context3.hip`` hold no device code of their
+own, so they compile with g++ against a model of the HIP runtime
+(``host_model/hip/hip_runtime.h``) and of the launches (``host_model/model.cpp``):
+device memory has addresses and every lattice holds its update count instead of
+populations.  Each scenario checks that the addresses, the order and the
+lifetimes the contexts use belong together, also where a GPU could only show a
+mistake by a fault.
+"""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+MODEL = os.path.join(HERE, "host_model")
+CSRC = os.path.join(ROOT, "paper_2607_20650_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def scenarios(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host_model") / "scenarios")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", MODEL, "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+                    "-x", "c++", os.path.join(CSRC, "context.hip"), os.path.join(CSRC, "context3.hip"),
+                    os.path.join(MODEL, "model.cpp"), os.path.join(MODEL, "scenarios.cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("name", ["captured_readout", "captured_load", "captured_3d"])
+def test_scenario(scenarios, name):
+    r = subprocess.run([scenarios, name], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout[:2000]
