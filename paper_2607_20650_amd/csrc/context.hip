@@ -654,10 +654,12 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     const int most = c->bundle > 0 ? c->plan.kk : 1;
     if (n > 0 && c->edge_elems && most > 1) c->edges_old = true;
     if (n > 0 && c->edges_old && most == 1) {
+        // a captured fill runs when it is replayed: updates before that fill
+        // the buffers for themselves
         const hipError_t e = launch_edge_fill(c->state, c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                                               c->edge[c->t & 1], c->stream);
         if (e != hipSuccess) return c->check(e, "edge fill");
-        c->edges_old = false;
+        c->edges_old = capturing(c->stream);
     }
     // A graph of few launches costs the host more than they do: 128 x 64, 200
     // updates as 6 graphs of 3 launches and one more 207 us, as 17 launches
@@ -774,7 +776,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     if (e == hipSuccess && c->edge_elems)
         e = launch_edge_fill(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                              c->edge[c->t & 1], c->stream);
-    c->edges_old = false;
+    c->edges_old = c->edges_old && capturing(c->stream);
     if (e == hipSuccess && c->obuf && c->state_now() == ST_SWAP)
         e = launch_aa_outlet_fill(c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), c->obuf, c->stream);
     if (borrow) {

@@ -144,11 +144,35 @@ void captured_load()
         lbm_step(a.c, 36);
         const Graph g = capture(a.stream, [&] { lbm_set_state(a.c, f, 1); });
         for (int n : {2, 8, 12, 34}) {
+            const long t = a.count();
             lbm_step(a.c, n);
+            expect(a.count() == t + n, name + "updates before a replay");
             replay(g);
             expect(a.count() == 1000, name + "load after " + std::to_string(n));
             lbm_step(a.c, 6);
             expect(a.count() == 1006, name + "updates after a load");
+        }
+    });
+}
+
+// Eager updates between a capture and its first replay, and a capture that is
+// never replayed.
+void eager_before_replay()
+{
+    each_scheme([](int scheme, const std::string& name) {
+        for (bool replayed : {true, false}) {
+            Sim a(scheme);
+            lbm_step(a.c, 36);
+            const Graph g = capture(a.stream, [&] { lbm_step(a.c, 2); });
+            lbm_step(a.c, 2);
+            long t = 38;
+            expect(a.count() == t, name + "updates before the first replay");
+            for (int n : {32, 2, 40}) {
+                if (replayed) replay(g), t += 2;
+                lbm_step(a.c, n);
+                t += n;
+                expect(a.count() == t, name + "updates after a replay");
+            }
         }
     });
 }
@@ -184,6 +208,7 @@ void captured_3d()
 const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_readout", captured_readout},
     {"captured_load", captured_load},
+    {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
 };
 

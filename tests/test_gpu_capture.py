@@ -81,7 +81,7 @@ def test_captured_readouts_report_the_current_state(scheme):
         assert np.array_equal(sim.populations(), ref.populations()), (scheme, n)
 
 
-@pytest.mark.parametrize("scheme", ["LPTL", "NPTL", "PUSH", "AA"])
+@pytest.mark.parametrize("scheme", ALL_SCHEMES)
 def test_captured_state_load_replaces_the_current_state(scheme):
     import torch
     sim, ref = _pair(scheme)
@@ -98,6 +98,20 @@ def test_captured_state_load_replaces_the_current_state(scheme):
         assert np.array_equal(sim.populations(), ref.populations()), (scheme, n)
         sim.step(6)
         ref.step(6)
+        assert np.array_equal(sim.populations(), ref.populations()), (scheme, n)
+
+
+@pytest.mark.parametrize("scheme", ALL_SCHEMES)
+def test_eager_steps_between_capture_and_first_replay(scheme):
+    sim, ref = _pair(scheme)
+    g = _capture(sim, lambda: sim.step(2))
+    for s in (sim, ref):
+        s.step(2)
+    assert np.array_equal(sim.populations(), ref.populations()), scheme
+    for n in (32, 2, 40):
+        _replay(sim, g)
+        sim.step(n)
+        ref.step(2 + n)
         assert np.array_equal(sim.populations(), ref.populations()), (scheme, n)
 
 
