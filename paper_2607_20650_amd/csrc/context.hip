@@ -82,6 +82,7 @@ struct lbm_ctx {
     bool edges_old = false; // one-lattice tiled schemes: edge[] is not that of the state
     FusedPlan plan; // several updates per launch
     bool captured = false; // calls have been captured
+    bool load_captured = false; // of lbm_set_state
     int32_t bundle = 32;
     int32_t block = 256;
     hipGraph_t graph[4] = {}; // by graph_key
@@ -255,10 +256,11 @@ int tile_threads(int scheme, int layout, int prec, int tx, int ty)
 }
 
 // A one-lattice scheme gives its second lattice back, for other memory; single
-// updates in place from then on.
+// updates in place from then on.  Captured updates and readouts refer to the
+// one that holds the state, but a captured load of AA to both.
 bool give_back(lbm_ctx* c)
 {
-    if (is_two_lattice(c->grid.scheme) || !c->lat_raw[1]) return false;
+    if (is_two_lattice(c->grid.scheme) || !c->lat_raw[1] || c->load_captured || capturing(c->stream)) return false;
     if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
     drop_graphs(c);
     if (c->cur) {
@@ -764,6 +766,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     }
     // the push state is built from the pull form through a second lattice;
     // AA, which has one, borrows a temporary one
+    if (c->captured && capturing(c->stream)) c->load_captured = true;
     void* tmp = c->other_lat();
     const bool borrow = c->state_now() == ST_PUSH && !tmp;
     if (borrow && hipMalloc(&tmp, (size_t)c->lat_elems * c->elem) != hipSuccess)

@@ -52,6 +52,7 @@ struct lbm3_ctx {
     int64_t t = 0;
     int now = 0; // the lattice that holds the state
     bool several = false; // FUSED3 updates per launch
+    bool captured = false, load_captured = false; // calls (of lbm3_set_state) have been captured
     HostRing ring;
     bool poisoned = false;
     std::string err;
@@ -99,19 +100,23 @@ lbm_status create3_error(lbm_status s, const std::string& msg)
 }
 
 // What launches of several updates hold beside the state goes back, for other
-// memory; single updates from then on.
+// memory; single updates from then on.  Not what a captured call refers to: any
+// call the link words, a load of AA also the second lattice.
 bool give_back3(lbm3_ctx* c)
 {
-    if (!c->links || hipStreamSynchronize(c->stream) != hipSuccess) return false;
-    if (c->aa()) {
+    const bool lattice = c->aa() && c->lat[1] && !c->load_captured, links = c->links && !c->captured;
+    if ((!lattice && !links) || capturing(c->stream) || hipStreamSynchronize(c->stream) != hipSuccess) return false;
+    if (lattice) {
         if (c->now) std::swap(c->lat[0], c->lat[1]);
         c->now = 0;
         (void)hipFree(c->lat[1]);
         c->lat[1] = nullptr;
     }
-    (void)hipFree(c->links);
-    c->links = nullptr;
-    c->kp.links = nullptr;
+    if (links) {
+        (void)hipFree(c->links);
+        c->links = nullptr;
+        c->kp.links = nullptr;
+    }
     c->several = false;
     return true;
 }
@@ -132,7 +137,9 @@ bool alloc3(lbm3_ctx* c, void** p, size_t bytes)
 // after every even number.
 void watch_capture3(lbm3_ctx* c)
 {
-    if (c->several && capturing(c->stream)) c->several = false;
+    if (c->captured || !capturing(c->stream)) return;
+    c->captured = true;
+    c->several = false;
 }
 
 lbm_status ensure_readout3(lbm3_ctx* c)
@@ -382,6 +389,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
         if (e != hipSuccess) return c->check(e, "state upload");
         src = c->readout;
     }
+    if (c->captured && capturing(c->stream)) c->load_captured = true;
     // the push form is built from the pull form through a second lattice
     void* tmp = c->lat[c->now ^ 1];
     const bool borrow = c->state() == ST_PUSH && !tmp;

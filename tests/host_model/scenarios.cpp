@@ -205,11 +205,71 @@ void captured_3d()
     }
 }
 
+// Memory held for several updates per launch goes back when an allocation
+// fails, but nothing that a captured call refers to.
+void given_back()
+{
+    double d[5];
+    for (int scheme : {S_NPTL, S_AA})
+        for (bool several : {true, false})
+            for (int captured : {0, 1, 2}) { // nothing, an update and a readout, a load
+                if (scheme == S_AA && !several && captured == 2) continue; // allocates, which a capture refuses
+                serves3 = several;
+                Sim3 a(scheme);
+                const std::string name = std::string("D3Q19 ") + NAMES[scheme] + " captured " + std::to_string(captured);
+                float* f = nullptr;
+                (void)hipMalloc(&f, 4096);
+                set_count(f, 1000);
+                lbm3_step(a.c, 4);
+                const Graph g = capture(a.stream, [&] {
+                    if (captured == 1) lbm3_step(a.c, 2), lbm3_macros(a.c, f + 64, nullptr, 1);
+                    if (captured == 2) lbm3_set_state(a.c, f, 1);
+                });
+                const size_t before = dev.free_bytes;
+                dev.largest = 0;
+                expect(lbm3_diag(a.c, d) == LBM_ENOMEM, name + ": diagnostics without memory");
+                dev.largest = SIZE_MAX;
+                if (!captured) expect(dev.free_bytes > before, name + ": memory goes back");
+                replay(g);
+                const long t = captured == 2 ? 1000 : captured ? 6 : 4;
+                expect(a.count() == t, name + ": state");
+                lbm3_step(a.c, 6);
+                expect(a.count() == t + 6, name + ": updates after");
+                expect(lbm3_diag(a.c, d) == LBM_OK, name + ": diagnostics");
+            }
+    for (int scheme : {S_NPOL, S_NSOL, S_AA})
+        for (int captured : {0, 1, 2}) {
+            plan = FusedPlan{8, 0, 64};
+            Sim a(scheme);
+            const std::string name = std::string(NAMES[scheme]) + " captured " + std::to_string(captured);
+            float* f = nullptr;
+            (void)hipMalloc(&f, 4096);
+            set_count(f, 1000);
+            lbm_step(a.c, 8);
+            const Graph g = capture(a.stream, [&] {
+                if (captured == 1) lbm_step(a.c, 2), lbm_macros(a.c, f + 64, nullptr, 1);
+                if (captured == 2) lbm_set_state(a.c, f, 1);
+            });
+            const size_t before = dev.free_bytes;
+            dev.largest = 0;
+            expect(lbm_diag(a.c, d) == LBM_ENOMEM, name + ": diagnostics without memory");
+            dev.largest = SIZE_MAX;
+            if (captured < 2) expect(dev.free_bytes > before, name + ": memory goes back");
+            replay(g);
+            const long t = captured == 2 ? 1000 : captured ? 10 : 8;
+            expect(a.count() == t, name + ": state");
+            lbm_step(a.c, 6);
+            expect(a.count() == t + 6, name + ": updates after");
+            expect(lbm_diag(a.c, d) == LBM_OK, name + ": diagnostics");
+        }
+}
+
 const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_readout", captured_readout},
     {"captured_load", captured_load},
     {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
+    {"given_back", given_back},
 };
 
 } // namespace
