@@ -26,6 +26,15 @@
  *     on_device != 0 (they must then be device pointers valid on the context's
  *     device and stream), else they are host pointers and the call
  *     synchronizes the stream before returning.
+ *   - Spare memory: a one-lattice scheme also allocates a second lattice, while
+ *     one takes at most 1.5 GiB, to do several updates per launch, and a D3Q19
+ *     simulation in the stream or blocked layout 4 bytes per node that spare its
+ *     boundary nodes the look at their neighbours.  All simulations of the
+ *     process together hold at most 1/32 of a device's memory this way, and
+ *     take it only while 1/16 of that memory stays free.  It goes back when a
+ *     device allocation of any simulation or server fails, from all simulations
+ *     that no other thread is in a call on and no captured call refers to: they
+ *     then go on without, slower, with the same results.
  */
 #ifndef LBM_H
 #define LBM_H
@@ -56,7 +65,8 @@ typedef enum {
     LBM_AA = 5       /* in-place AA streaming (Bailey et al.), the state-of-the-art one-lattice
                         scheme Section 3.3 cites and Section 6 names as the next step: even
                         updates are local, odd updates exchange pairwise with the neighbours;
-                        one lattice, no buffer grid, 3 values per row of outlet side buffer */
+                        no buffer grid, 3 values per row of outlet side buffer.  As the other
+                        one-lattice schemes it needs one lattice; see "spare memory" below */
 } lbm_scheme;
 
 /* Data layouts (paper Section 3.2, Fig. 2). */
@@ -224,8 +234,7 @@ typedef struct {
     int32_t tile_x, tile_y;  /* tile chosen for tiled schemes (0 for LPTL) */
     int32_t block;           /* threads per block of the update kernel */
     int32_t bundle;          /* updates per cached HIP graph (0 = no graphs) */
-    int64_t device_bytes;    /* device memory owned by the context (a one-lattice scheme holds a second
-                                lattice, for launches of several updates, while one takes at most 1.5 GiB) */
+    int64_t device_bytes;    /* device memory owned by the context, spare memory included */
     int64_t fluid_nodes;     /* fluid + outlet nodes */
 } lbm_info;
 
@@ -335,8 +344,9 @@ void lbm_server_destroy(lbm_server* s);
  *     opposite(i) = 18 - i.  Weights 1/3 (rest), 1/18 (|c| = 1), 1/36.
  *   - Populations crossing the ABI are shifted (f - w), FP32.
  *   - Schemes: LBM_NPTL (two lattices, one-step pull, tile_x * tile_y nodes
- *     of one z plane per block) and LBM_AA (one lattice in place).  Layouts: LBM_STREAM (SoA), LBM_COLLISION (AoS) and
- *     LBM_BLOCKED (AoSoA, blocks of 64 nodes).
+ *     of one z plane per block) and LBM_AA (one lattice, a second one as spare
+ *     memory).  Layouts: LBM_STREAM (SoA), LBM_COLLISION (AoS) and LBM_BLOCKED
+ *     (AoSoA, blocks of 64 nodes).
  *     Precisions: all of lbm_precision.
  *   - Status, error text, streams and the on_device convention are those of
  *     the 2-D entry points. */

@@ -54,7 +54,7 @@ int state_of(int scheme)
 
 } // namespace
 
-struct lbm_ctx {
+struct lbm_ctx final : SpareOwner {
     lbm_grid grid{};
     lbm_bc bc{};
     double tau = 0;
@@ -123,6 +123,7 @@ struct lbm_ctx {
         return p;
     }
     KParams view() const { return at((int)(t & 1), false); }
+    bool give_back() override;
 };
 
 namespace {
@@ -139,6 +140,7 @@ void drop_graphs(lbm_ctx* c)
 
 void free_all(lbm_ctx* c)
 {
+    Spares::get().leave(c);
     drop_graphs(c);
     for (int k = 0; k < 2; ++k) {
         if (c->lat_raw[k]) (void)hipFree(c->lat_raw[k]);
@@ -255,40 +257,25 @@ int tile_threads(int scheme, int layout, int prec, int tx, int ty)
     return tx * ty;
 }
 
-// A one-lattice scheme gives its second lattice back, for other memory; single
-// updates in place from then on.  Captured updates and readouts refer to the
-// one that holds the state, but a captured load of AA to both.
-bool give_back(lbm_ctx* c)
-{
-    if (is_two_lattice(c->grid.scheme) || !c->lat_raw[1] || c->load_captured || capturing(c->stream)) return false;
-    if (hipStreamSynchronize(c->stream) != hipSuccess) return false;
-    drop_graphs(c);
-    if (c->cur) {
-        std::swap(c->lat[0], c->lat[1]);
-        std::swap(c->lat_raw[0], c->lat_raw[1]);
-        c->cur = 0;
-    }
-    (void)hipFree(c->lat_raw[1]);
-    c->lat[1] = c->lat_raw[1] = nullptr;
-    c->bytes -= ((int64_t)c->lat_elems + 2 * c->guard) * c->elem;
-    c->plan = FusedPlan{};
-    return true;
-}
-
 lbm_status alloc(lbm_ctx* c, void** p, size_t bytes)
 {
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        if (give_back(c)) e = hipMalloc(p, bytes);
-    }
-    if (e != hipSuccess) {
-        *p = nullptr;
-        (void)hipGetLastError();
-        return LBM_ENOMEM;
-    }
+    if (device_alloc(p, bytes, c) != hipSuccess) return LBM_ENOMEM;
     c->bytes += (int64_t)bytes;
     return LBM_OK;
+}
+
+// The second lattice of a one-lattice scheme, while there is memory to spare.
+bool alloc_spare(lbm_ctx* c, size_t bytes)
+{
+    if (!Spares::get().take(c, bytes)) return false;
+    if (hipMalloc(&c->lat_raw[1], bytes) == hipSuccess) {
+        c->bytes += (int64_t)bytes;
+        return true;
+    }
+    (void)hipGetLastError();
+    c->lat_raw[1] = nullptr;
+    c->spare -= bytes;
+    return false;
 }
 
 // The one update after update count t (its parity is what matters), state in
@@ -393,6 +380,27 @@ lbm_status ensure_readout(lbm_ctx* c)
 }
 
 } // namespace
+
+// A one-lattice scheme gives its second lattice back, for other memory; single
+// updates in place from then on.  Captured updates and readouts refer to the
+// one that holds the state, but a captured load of AA to both.
+bool lbm_ctx::give_back()
+{
+    if (!spare || load_captured || capturing(stream)) return false;
+    if (hipStreamSynchronize(stream) != hipSuccess) return false;
+    drop_graphs(this);
+    if (cur) {
+        std::swap(lat[0], lat[1]);
+        std::swap(lat_raw[0], lat_raw[1]);
+        cur = 0;
+    }
+    (void)hipFree(lat_raw[1]);
+    lat[1] = lat_raw[1] = nullptr;
+    bytes -= (int64_t)spare;
+    spare = 0;
+    plan = FusedPlan{};
+    return true;
+}
 
 // ------------------------------------------------------------ shared setup
 // Validation and constants shared by simulations and served requests.
@@ -601,20 +609,22 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     if (st == LBM_OK) st = alloc(c, (void**)&c->types, (size_t)(g.px * ny));
     if (st == LBM_OK) st = alloc(c, (void**)&c->links, (size_t)(g.px * ny) * sizeof(uint32_t));
     uint8_t* dflags = nullptr;
-    if (st == LBM_OK && hipMalloc(&dflags, (size_t)N) != hipSuccess) {
-        dflags = nullptr;
-        st = LBM_ENOMEM;
-    }
+    if (st == LBM_OK && device_alloc((void**)&dflags, (size_t)N, nullptr) != hipSuccess) st = LBM_ENOMEM;
     // last: without memory for it every update is one in place
+    std::unique_lock<std::mutex> call(c->mu);
+    auto drop = [&] {
+        free_all(c); // out of other threads' sight first
+        call.unlock();
+        delete c;
+    };
     if (st == LBM_OK && !is_two_lattice(grid->scheme) && raw_bytes <= SPARE_MOST && !is_neumann_inlet(bc->x_axis)) {
         c->plan = fused_plan(c->kp, grid->scheme, grid->layout, grid->precision);
-        if (c->plan.kk > 1 && alloc(c, &c->lat_raw[1], raw_bytes) != LBM_OK) c->plan = FusedPlan{};
+        if (c->plan.kk > 1 && !alloc_spare(c, raw_bytes)) c->plan = FusedPlan{};
     }
     for (int k = 0; k < 2; ++k)
         if (c->lat_raw[k]) c->lat[k] = (char*)c->lat_raw[k] + (size_t)c->guard * c->elem;
     if (st != LBM_OK) {
-        free_all(c);
-        delete c;
+        drop();
         return create_error(LBM_ENOMEM, "device memory exhausted");
     }
     c->kp.types = c->types;
@@ -635,8 +645,7 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
     (void)hipFree(dflags);
     if (e != hipSuccess) {
         std::string msg = std::string("initialisation failed: ") + hipGetErrorString(e);
-        free_all(c);
-        delete c;
+        drop();
         return create_error(LBM_EDEVICE, msg);
     }
     c->block = grid->scheme == LBM_LPTL ? lptl_block_size(grid->layout, grid->precision)
@@ -650,6 +659,7 @@ lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, co
 lbm_status lbm_step(lbm_ctx* c, int64_t n)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
     watch_capture(c);
@@ -691,6 +701,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
 lbm_status lbm_set_bundle(lbm_ctx* c, int32_t k)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (k < 0 || k > 4096) return c->fail(LBM_EINVAL, "bundle must be in [0, 4096]");
     if (k != c->bundle) {
         lbm_status st = c->check(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
@@ -704,6 +715,7 @@ lbm_status lbm_set_bundle(lbm_ctx* c, int32_t k)
 lbm_status lbm_sync(lbm_ctx* c)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     return c->check(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
 }
@@ -711,6 +723,7 @@ lbm_status lbm_sync(lbm_ctx* c)
 lbm_status lbm_macros(lbm_ctx* c, float* rho, float* u, int on_device)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (!rho && !u) return LBM_OK;
     watch_capture(c);
@@ -734,6 +747,7 @@ lbm_status lbm_macros(lbm_ctx* c, float* rho, float* u, int on_device)
 lbm_status lbm_get_populations(lbm_ctx* c, float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
@@ -753,6 +767,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, float* f, int on_device)
 lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
@@ -769,7 +784,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     if (c->captured && capturing(c->stream)) c->load_captured = true;
     void* tmp = c->other_lat();
     const bool borrow = c->state_now() == ST_PUSH && !tmp;
-    if (borrow && hipMalloc(&tmp, (size_t)c->lat_elems * c->elem) != hipSuccess)
+    if (borrow && device_alloc(&tmp, (size_t)c->lat_elems * c->elem, c) != hipSuccess)
         return c->fail(LBM_ENOMEM, "temporary lattice for the state load");
     hipError_t e = hipSuccess;
     if (c->rin) e = launch_inlet_density_fill(c->kp, src, c->rin + (c->t & 1) * c->grid.ny, c->stream);
@@ -795,6 +810,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
 lbm_status lbm_diag(lbm_ctx* c, double out[4])
 {
     if (!c || !out) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     const Geometry& g = c->kp.g;
     if (!c->u_prev) {
@@ -831,6 +847,7 @@ lbm_status lbm_diag(lbm_ctx* c, double out[4])
 lbm_status lbm_diag_noalloc(lbm_ctx* c, double* u_prev, int32_t have_prev, double* out)
 {
     if (!c || !out || (have_prev && !u_prev)) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     const size_t need = (size_t)diag_partials() + 8;
     if (need > NOALLOC_SCRATCH_DOUBLES)
@@ -850,6 +867,7 @@ lbm_status lbm_diag_noalloc(lbm_ctx* c, double* u_prev, int32_t have_prev, doubl
 lbm_status lbm_get_info(const lbm_ctx* c, lbm_info* info)
 {
     if (!c || !info) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     info->steps = c->t;
     info->nx = c->grid.nx;
     info->ny = c->grid.ny;

@@ -33,7 +33,7 @@ void feq3_shifted(const double u[3], float* out)
 
 } // namespace
 
-struct lbm3_ctx {
+struct lbm3_ctx final : SpareOwner {
     lbm3_grid grid{};
     KParams3 kp{};
     int elem = 4;
@@ -73,12 +73,15 @@ struct lbm3_ctx {
     int state() const { return aa() ? ((t & 1) ? ST_SWAP : ST_PUSH) : ST_PULL; }
     void* cur() const { return lat[now]; }
     int64_t nodes() const { return grid.nx * grid.ny * grid.nz; }
+    size_t link_bytes() const { return (size_t)(kp.g.plane * grid.nz) * sizeof(uint32_t); }
+    bool give_back() override;
 };
 
 namespace {
 
 void free3(lbm3_ctx* c)
 {
+    Spares::get().leave(c);
     for (void* p : {c->lat[0], c->lat[1], c->obuf, (void*)c->types, (void*)c->links, (void*)c->readout, (void*)c->u_prev,
                     (void*)c->partials, (void*)c->dout})
         if (p) (void)hipFree(p);
@@ -99,35 +102,14 @@ lbm_status create3_error(lbm_status s, const std::string& msg)
     return s;
 }
 
-// What launches of several updates hold beside the state goes back, for other
-// memory; single updates from then on.  Not what a captured call refers to: any
-// call the link words, a load of AA also the second lattice.
-bool give_back3(lbm3_ctx* c)
+// Spare memory, if there is any: *p stays null otherwise.
+bool alloc_spare3(lbm3_ctx* c, void** p, size_t bytes)
 {
-    const bool lattice = c->aa() && c->lat[1] && !c->load_captured, links = c->links && !c->captured;
-    if ((!lattice && !links) || capturing(c->stream) || hipStreamSynchronize(c->stream) != hipSuccess) return false;
-    if (lattice) {
-        if (c->now) std::swap(c->lat[0], c->lat[1]);
-        c->now = 0;
-        (void)hipFree(c->lat[1]);
-        c->lat[1] = nullptr;
-    }
-    if (links) {
-        (void)hipFree(c->links);
-        c->links = nullptr;
-        c->kp.links = nullptr;
-    }
-    c->several = false;
-    return true;
-}
-
-bool alloc3(lbm3_ctx* c, void** p, size_t bytes)
-{
+    if (!Spares::get().take(c, bytes)) return false;
     if (hipMalloc(p, bytes) == hipSuccess) return true;
     (void)hipGetLastError();
-    if (give_back3(c) && hipMalloc(p, bytes) == hipSuccess) return true;
-    (void)hipGetLastError();
     *p = nullptr;
+    c->spare -= bytes;
     return false;
 }
 
@@ -145,12 +127,36 @@ void watch_capture3(lbm3_ctx* c)
 lbm_status ensure_readout3(lbm3_ctx* c)
 {
     if (c->readout) return LBM_OK;
-    if (!alloc3(c, (void**)&c->readout, (size_t)c->nodes() * Q3 * sizeof(float)))
+    if (device_alloc((void**)&c->readout, (size_t)c->nodes() * Q3 * sizeof(float), c) != hipSuccess)
         return c->fail(LBM_ENOMEM, "readout buffer allocation failed");
     return LBM_OK;
 }
 
 } // namespace
+
+// What launches of several updates hold beside the state goes back, for other
+// memory; single updates from then on.  Not what a captured call refers to: any
+// call the link words, a load of AA also the second lattice.
+bool lbm3_ctx::give_back()
+{
+    const bool lattice = aa() && lat[1] && !load_captured, words = links && !captured;
+    if ((!lattice && !words) || capturing(stream) || hipStreamSynchronize(stream) != hipSuccess) return false;
+    if (lattice) {
+        if (now) std::swap(lat[0], lat[1]);
+        now = 0;
+        (void)hipFree(lat[1]);
+        lat[1] = nullptr;
+        spare -= (size_t)lat_elems * elem;
+    }
+    if (words) {
+        (void)hipFree(links);
+        links = nullptr;
+        kp.links = nullptr;
+        spare -= link_bytes();
+    }
+    several = false;
+    return true;
+}
 
 extern "C" {
 
@@ -254,37 +260,28 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
         c->own_stream = true;
     }
     const size_t lat_bytes = (size_t)c->lat_elems * c->elem;
-    bool ok = hipMalloc(&c->lat[0], lat_bytes) == hipSuccess;
-    if (ok && grid->scheme == LBM_NPTL) ok = hipMalloc(&c->lat[1], lat_bytes) == hipSuccess;
-    if (ok && grid->scheme == LBM_AA && g.xa == AX_INOUT)
-        ok = hipMalloc(&c->obuf, (size_t)(5 * ny * nz) * c->elem) == hipSuccess;
-    if (ok) ok = hipMalloc((void**)&c->types, (size_t)(g.plane * nz)) == hipSuccess;
+    auto get = [](void** p, size_t bytes) { return device_alloc(p, bytes, nullptr) == hipSuccess; };
+    bool ok = get(&c->lat[0], lat_bytes);
+    if (ok && grid->scheme == LBM_NPTL) ok = get(&c->lat[1], lat_bytes);
+    if (ok && grid->scheme == LBM_AA && g.xa == AX_INOUT) ok = get(&c->obuf, (size_t)(5 * ny * nz) * c->elem);
+    if (ok) ok = get((void**)&c->types, (size_t)(g.plane * nz));
     uint8_t* dflags = nullptr;
-    if (ok) ok = hipMalloc((void**)&dflags, (size_t)N) == hipSuccess;
+    if (ok) ok = get((void**)&dflags, (size_t)N);
     if (!ok) {
-        (void)hipGetLastError();
         if (dflags) (void)hipFree(dflags);
         free3(c);
         delete c;
         return create3_error(LBM_ENOMEM, "device memory exhausted");
     }
     c->kp.types = c->types;
+    std::unique_lock<std::mutex> call(c->mu);
     // optional: link words (without them boundary nodes look up their
     // neighbours' types) and, for several updates per launch of AA, a second
     // lattice
-    if (grid->layout != LBM_COLLISION &&
-        hipMalloc((void**)&c->links, (size_t)(g.plane * nz) * sizeof(uint32_t)) != hipSuccess) {
-        c->links = nullptr;
-        (void)hipGetLastError();
-    }
+    if (grid->layout != LBM_COLLISION) (void)alloc_spare3(c, (void**)&c->links, c->link_bytes());
     c->several = c->links && fused3_serves(g, grid->layout, grid->precision);
-    if (c->several && grid->scheme == LBM_AA) {
-        c->several = lat_bytes <= SPARE_MOST && hipMalloc(&c->lat[1], lat_bytes) == hipSuccess;
-        if (!c->several) {
-            c->lat[1] = nullptr;
-            (void)hipGetLastError();
-        }
-    }
+    if (c->several && grid->scheme == LBM_AA)
+        c->several = lat_bytes <= SPARE_MOST && alloc_spare3(c, &c->lat[1], lat_bytes);
     c->kp.links = c->links;
     hipError_t e = hipMemcpyAsync(dflags, flags, (size_t)N, hipMemcpyHostToDevice, c->stream);
     if (e == hipSuccess) e = launch3_types(g, dflags, c->types, c->stream);
@@ -296,7 +293,8 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
     (void)hipFree(dflags);
     if (e != hipSuccess) {
         std::string msg = std::string("initialisation failed: ") + hipGetErrorString(e);
-        free3(c);
+        free3(c); // out of other threads' sight first
+        call.unlock();
         delete c;
         return create3_error(LBM_EDEVICE, msg);
     }
@@ -307,6 +305,7 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
 lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
     watch_capture3(c);
@@ -338,6 +337,7 @@ lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
 lbm_status lbm3_macros(lbm3_ctx* c, float* rho, float* u, int on_device)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     watch_capture3(c);
     if (on_device)
@@ -359,6 +359,7 @@ lbm_status lbm3_macros(lbm3_ctx* c, float* rho, float* u, int on_device)
 lbm_status lbm3_get_populations(lbm3_ctx* c, float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     watch_capture3(c);
     if (on_device)
@@ -378,6 +379,7 @@ lbm_status lbm3_get_populations(lbm3_ctx* c, float* f, int on_device)
 lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
 {
     if (!c || !f) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     watch_capture3(c);
     const float* src = f;
@@ -393,9 +395,8 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
     // the push form is built from the pull form through a second lattice
     void* tmp = c->lat[c->now ^ 1];
     const bool borrow = c->state() == ST_PUSH && !tmp;
-    if (borrow && !alloc3(c, &tmp, (size_t)c->lat_elems * c->elem)) {
+    if (borrow && device_alloc(&tmp, (size_t)c->lat_elems * c->elem, c) != hipSuccess)
         return c->fail(LBM_ENOMEM, "temporary lattice for the state load");
-    }
     hipError_t e = launch3_set_state(c->state(), c->grid.layout, c->grid.precision, c->kp, src, c->cur(), tmp,
                                      c->stream);
     if (e == hipSuccess && c->obuf && c->state() == ST_SWAP)
@@ -413,9 +414,10 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
 lbm_status lbm3_diag(lbm3_ctx* c, double out[5])
 {
     if (!c || !out) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     const Geometry3& g = c->kp.g;
-    auto get = [&](void** p, size_t bytes) { return *p || alloc3(c, p, bytes); };
+    auto get = [&](void** p, size_t bytes) { return *p || device_alloc(p, bytes, c) == hipSuccess; };
     if (!get((void**)&c->u_prev, (size_t)(3 * g.plane * g.nz) * sizeof(double)) ||
         !get((void**)&c->partials, (size_t)diag3_partials() * sizeof(double)) ||
         !get((void**)&c->dout, 8 * sizeof(double)))
@@ -441,6 +443,7 @@ lbm_status lbm3_diag(lbm3_ctx* c, double out[5])
 lbm_status lbm3_sync(lbm3_ctx* c)
 {
     if (!c) return LBM_EINVAL;
+    const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     return c->check(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
 }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -41,6 +42,110 @@ inline bool capturing(hipStream_t s)
     if (hipStreamIsCapturing(s, &st) == hipSuccess) return st == hipStreamCaptureStatusActive;
     (void)hipGetLastError();
     return false;
+}
+
+// A simulation that may hold memory only to be faster: the second lattice of a
+// one-lattice scheme, the link words of a D3Q19 one.
+class SpareOwner {
+public:
+    // Held by every call on the simulation: between its calls another thread
+    // whose allocation fails may ask for the memory.
+    mutable std::mutex mu;
+    // Frees what can be spared (mu held); whether there was any.
+    virtual bool give_back() = 0;
+    std::atomic<size_t> spare{0}; // bytes held
+
+protected:
+    ~SpareOwner() = default;
+
+private:
+    friend class Spares;
+    SpareOwner *next_ = nullptr, **link_ = nullptr; // in the list of owners
+    int device_ = 0;
+};
+
+// The owners of spare memory in the process.  All of them together hold at
+// most 1/32 of a device's memory (9 of 288 GB), and take more only while 1/16
+// of it stays free; when an allocation of any simulation or serving engine
+// fails, all give back what they can before it is tried once more.  (Without
+// this a second simulation, or other users of the device, ran out of memory
+// where the one-lattice schemes had left room for them.)
+class Spares {
+public:
+    // Whether o may allocate `bytes` of spare memory on the current device;
+    // counts them as held.
+    bool take(SpareOwner* o, size_t bytes)
+    {
+        size_t free = 0, total = 0;
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipMemGetInfo(&free, &total) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        const std::lock_guard<std::mutex> lock(mu_);
+        size_t held = bytes;
+        for (SpareOwner* q = first_; q; q = q->next_)
+            if (q->device_ == dev) held += q->spare;
+        if (held > total / 32 || free < bytes + total / 16) return false;
+        o->spare += bytes;
+        if (!o->link_) {
+            o->device_ = dev;
+            o->next_ = first_;
+            o->link_ = &first_;
+            if (first_) first_->link_ = &o->next_;
+            first_ = o;
+        }
+        return true;
+    }
+    // The owner ends; no other thread asks it for memory from here on.
+    void leave(SpareOwner* o)
+    {
+        const std::lock_guard<std::mutex> lock(mu_);
+        if (!o->link_) return;
+        *o->link_ = o->next_;
+        if (o->next_) o->next_->link_ = o->link_;
+        o->link_ = nullptr;
+    }
+    // Everything that owners on the current device can spare goes back, but for
+    // `self` and owners in a call of another thread.  Whether there was any.
+    bool reclaim(const SpareOwner* self)
+    {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return false;
+        const std::lock_guard<std::mutex> lock(mu_);
+        bool any = false;
+        for (SpareOwner* q = first_; q; q = q->next_) {
+            if (q == self || q->device_ != dev) continue;
+            const std::unique_lock<std::mutex> call(q->mu, std::try_to_lock);
+            if (call.owns_lock() && q->give_back()) any = true;
+        }
+        return any;
+    }
+    static Spares& get()
+    {
+        static Spares* const p = new Spares(); // outlives every simulation
+        return *p;
+    }
+
+private:
+    std::mutex mu_;
+    SpareOwner* first_ = nullptr;
+};
+
+// hipMalloc for a call of `self` (null: of no simulation); *p is null on failure.
+inline hipError_t device_alloc(void** p, size_t bytes, SpareOwner* self)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        const bool own = self && self->give_back();
+        if (Spares::get().reclaim(self) || own) e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+    }
+    return e;
 }
 
 // Whether any flag is neither 0 nor 1.  No early exit, so that it vectorises.

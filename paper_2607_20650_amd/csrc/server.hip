@@ -421,15 +421,11 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
             return cleanup(LBM_EDEVICE, "hipEventCreate failed");
         s->free_events.push_back(ev);
     }
-    if (hipMalloc((void**)&s->pool, (size_t)s->budget) != hipSuccess) {
-        s->pool = nullptr;
-        (void)hipGetLastError();
-        return cleanup(LBM_ENOMEM, "cannot allocate the HBM budget");
-    }
+    auto get = [](void** p, size_t bytes) { return device_alloc(p, bytes, nullptr) == hipSuccess; };
+    if (!get((void**)&s->pool, (size_t)s->budget)) return cleanup(LBM_ENOMEM, "cannot allocate the HBM budget");
     s->free_list[0] = s->budget;
-    bool ok = hipMalloc((void**)&s->d_slots, sizeof(SlotDesc) * max_slots) == hipSuccess &&
-              hipMalloc((void**)&s->d_work, sizeof(WorkItem) * s->work_cap) == hipSuccess &&
-              hipMalloc((void**)&s->d_nwork, 2 * sizeof(int32_t)) == hipSuccess;
+    bool ok = get((void**)&s->d_slots, sizeof(SlotDesc) * max_slots) &&
+              get((void**)&s->d_work, sizeof(WorkItem) * s->work_cap) && get((void**)&s->d_nwork, 2 * sizeof(int32_t));
     for (int k = 0; k < 2 && ok; ++k)
         ok = hipHostMalloc((void**)&s->h_slots[k], sizeof(SlotDesc) * max_slots, hipHostMallocDefault) == hipSuccess &&
              hipHostMalloc((void**)&s->h_work[k], sizeof(WorkItem) * s->work_cap, hipHostMallocDefault) ==

@@ -109,6 +109,7 @@ hipError_t hipHostFree(void* p)
 }
 hipError_t hipMemGetInfo(size_t* free_bytes, size_t* total)
 {
+    const std::lock_guard<std::recursive_mutex> lock(mu);
     *free_bytes = dev.free_bytes;
     *total = dev.total;
     return hipSuccess;
@@ -199,6 +200,7 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, void*, char*, si
 hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t s)
 {
     if (s->capture) return done(hipErrorStreamCaptureUnsupported);
+    const std::lock_guard<std::recursive_mutex> lock(mu);
     ++dev.graph_launches;
     for (const Work& w : x->work) w();
     return hipSuccess;
@@ -391,5 +393,13 @@ hipError_t launch3_diag(int state, int, int, const KParams3&, const void* lat, d
 
 } // namespace lbm
 
-long count_at(const void* p) { return cell(p).t; }
-void set_count(const void* p, long t) { cell(p).t = t; }
+long count_at(const void* p)
+{
+    const std::lock_guard<std::recursive_mutex> lock(mu);
+    return cell(p).t;
+}
+void set_count(const void* p, long t)
+{
+    const std::lock_guard<std::recursive_mutex> lock(mu);
+    cell(p).t = t;
+}

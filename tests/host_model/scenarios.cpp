@@ -1,13 +1,16 @@
 // Scenarios of the simulation contexts on the modelled device, one per run:
 // scenarios <name>.  Prints what differs and exits with 1, or exits with 0.
+#include <atomic>
 #include <cstdio>
 #include <cstring>
 #include <functional>
 #include <map>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "lbm.h"
+#include "lbm_host.hpp"
 #include "model.hpp"
 
 using namespace lbm;
@@ -264,12 +267,128 @@ void given_back()
         }
 }
 
+// A simulation whose allocation fails gets the memory that others hold only to
+// be faster; they go on in place.
+void given_back_to_others()
+{
+    const size_t all = dev.free_bytes;
+    for (int scheme : {S_NPOL, S_NSOL, S_AA})
+        for (int n : {8, 16}) { // the state in the second lattice, in the first
+            plan = FusedPlan{8, 0, 64};
+            serves3 = true;
+            Sim a(scheme);
+            Sim3 b(S_AA), b2(S_NPTL);
+            lbm_step(a.c, n);
+            lbm3_step(b.c, 6);
+            lbm3_step(b2.c, 6);
+            const size_t before = dev.free_bytes;
+            dev.free_bytes = 0; // others use the rest of the device
+            {
+                Sim more(S_NPTL, 32, 16);
+                expect(more.status == LBM_OK, std::string("a simulation beside ") + NAMES[scheme]);
+                lbm_step(more.c, 40);
+                expect(more.count() == 40, "its state");
+            }
+            expect(dev.free_bytes > 0, "memory went back");
+            dev.free_bytes += before;
+            const int fused = dev.fused;
+            lbm_step(a.c, 16);
+            lbm3_step(b.c, 4);
+            lbm3_step(b2.c, 4);
+            expect(dev.fused == fused, "single updates from then on");
+            expect(a.count() == n + 16, std::string(NAMES[scheme]) + ": state afterwards");
+            expect(b.count() == 10 && b2.count() == 10, "D3Q19: state afterwards");
+        }
+    expect(dev.free_bytes == all, "all memory freed");
+}
+
+// Spare memory of all simulations together is bounded, and only taken while
+// enough stays free.
+void spare_memory_is_bounded()
+{
+    plan = FusedPlan{8, 0, 64};
+    auto fused = [](Sim& a) {
+        const int before = dev.fused;
+        lbm_step(a.c, 16);
+        return dev.fused > before;
+    };
+    size_t one; // spare bytes of one simulation
+    {
+        size_t f = dev.free_bytes;
+        Sim a(S_AA), b(S_NPTL);
+        lbm_info ia, ib;
+        lbm_get_info(a.c, &ia), lbm_get_info(b.c, &ib);
+        expect(ia.device_bytes == ib.device_bytes, "two lattices each");
+        expect(fused(a), "several updates per launch");
+        one = (f - dev.free_bytes) / 5;
+    }
+    dev.total = 32 * 10 * one;
+    dev.free_bytes = dev.total;
+    {
+        std::vector<Sim*> sims;
+        int with = 0;
+        for (int k = 0; k < 20; ++k) {
+            sims.push_back(new Sim(S_AA));
+            expect(sims.back()->status == LBM_OK, "creation");
+            with += fused(*sims.back());
+        }
+        expect(with > 3 && with < 20, "a bounded number of second lattices, not " + std::to_string(with));
+        for (Sim* s : sims) delete s;
+        expect(dev.free_bytes == dev.total, "all memory freed");
+    }
+    {
+        Sim a(S_AA);
+        expect(fused(a), "room again");
+    }
+    dev.free_bytes = dev.total / 20;
+    {
+        Sim a(S_AA);
+        expect(a.status == LBM_OK && !fused(a) && a.count() == 16, "in place while little is free");
+    }
+}
+
+// Simulations come, run and go on four threads while a fifth asks for their
+// spare memory again and again.
+void given_back_across_threads()
+{
+    plan = FusedPlan{8, 0, 64};
+    serves3 = true;
+    std::atomic<bool> stop{false};
+    std::atomic<int> bad{0};
+    std::vector<std::thread> th;
+    for (int k = 0; k < 4; ++k)
+        th.emplace_back([&, k] {
+            while (!stop) {
+                Sim a(k % 2 ? S_AA : S_NPOL);
+                Sim3 b(S_AA);
+                long t = 0;
+                for (int i = 0; i < 20; ++i) {
+                    lbm_step(a.c, 8 + 2 * i);
+                    lbm3_step(b.c, 8 + 2 * i);
+                    t += 8 + 2 * i;
+                    bad += a.count() != t || b.count() != t;
+                }
+            }
+        });
+    for (int i = 0; i < 300; ++i) {
+        void* p;
+        expect(device_alloc(&p, (size_t)1 << 50, nullptr) != hipSuccess, "more than there is");
+        std::this_thread::yield();
+    }
+    stop = true;
+    for (std::thread& t : th) t.join();
+    expect(!bad, "states");
+}
+
 const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_readout", captured_readout},
     {"captured_load", captured_load},
     {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
     {"given_back", given_back},
+    {"given_back_to_others", given_back_to_others},
+    {"given_back_across_threads", given_back_across_threads},
+    {"spare_memory_is_bounded", spare_memory_is_bounded},
 };
 
 } // namespace
