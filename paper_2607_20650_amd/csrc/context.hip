@@ -80,6 +80,7 @@ struct lbm_ctx final : SpareOwner {
     int64_t t = 0;
     int cur = 0;    // the lattice that holds the state
     bool edges_old = false; // one-lattice tiled schemes: edge[] is not that of the state
+    bool one_before = false; // the call before was of one update
     FusedPlan plan; // several updates per launch
     bool captured = false; // calls have been captured
     bool load_captured = false; // of lbm_set_state
@@ -663,7 +664,13 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
     watch_capture(c);
-    const int most = c->bundle > 0 ? c->plan.kk : 1;
+    // One update where the scheme's own kernel is the faster one: not right
+    // after launches of several, when its edge buffers would have to be refilled
+    // (calls of 8 and 1 updates in turn on 4096 x 1024 NPOL FP32: 27 us per
+    // update, 28.5 with the refill).
+    const bool own = n == 1 && c->plan.own && (!c->edges_old || c->one_before);
+    if (n > 0) c->one_before = n == 1;
+    const int most = c->bundle > 0 && !own ? c->plan.kk : 1;
     if (n > 0 && c->edge_elems && most > 1) c->edges_old = true;
     if (n > 0 && c->edges_old && most == 1) {
         // a captured fill runs when it is replayed: updates before that fill

@@ -212,6 +212,21 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // kernels; byte offsets within a row stay below OFF_NONE
     if (g.fw || p.rin != nullptr || g.px * stride * elem >= ((int64_t)1 << 30))
         return q;
+    // A call of one update of NPOL or NSOL passes from lattice to lattice here
+    // and in place in the scheme's own kernel.  That is the faster one where two
+    // lattices no longer stay in the cache: FP32 beyond 3 million nodes (1800 x
+    // 1400 NPOL stream 35 us here, 34 there, NSOL 35, 36; 2000 x 1800 65, 45 and
+    // 65, 48; 6000 x 3000 330, 299), 16-bit NSOL beyond 256 MB (4096 x 1024 FP16S
+    // 37, 40; 5000 x 1200 49, 53; 4096 x 2048 91, 73).  16-bit NPOL has a lean
+    // kernel that wins beyond 1.4 million (1600 x 1000 FP16S 19, 16; 4096 x 1024
+    // 36, 32; 1000 x 601 10, 11), and in the collision layout 2-byte stores apart
+    // from each other cost more than the exchange (700 x 500 FP16S 9.6, 8.0; 4096
+    // x 1024 67, 38; 513 x 257 6.6, 7.0).
+    if (scheme == S_NPOL || scheme == S_NSOL)
+        q.own = elem == 4                 ? g.nx * g.ny > 3000000
+                : layout == L_COLLISION   ? g.nx * g.ny > 250000
+                : scheme == S_NPOL        ? g.nx * g.ny > 1400000
+                                          : 18 * g.P * elem > ((int64_t)256 << 20);
     auto tiles = [&](int kk) {
         const int w = TILE_X - 2 * kk, h = TILE_ROWS - 2 * kk;
         return ((g.nx + w - 1) / w) * ((g.ny + h - 1) / h);

@@ -10,11 +10,12 @@ namespace lbm {
 hipError_t launch_update(int scheme, int layout, int prec, const KParams& p, int block, const void* src, void* dst,
                          const void* ein, void* eout, hipStream_t s);
 
-// How a two-lattice simulation runs several updates per launch.
+// How a simulation that holds two lattices runs several updates per launch.
 struct FusedPlan {
     int kk = 1;   // most updates per launch; 1: single updates only
     int tile = 0; // tiles of one node per thread instead of marching strips
     int rows = 0; // strips: rows per block
+    bool own = false; // NPOL, NSOL: a call of one update in place by the scheme's own kernel
 };
 FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec);
 // kk updates (1 .. q.kk) in one launch, src -> dst.

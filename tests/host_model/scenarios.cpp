@@ -208,6 +208,31 @@ void captured_3d()
     }
 }
 
+// Calls of one update of NPOL and NSOL: in place where the plan says so, but
+// not right after launches of several updates.
+void calls_of_one_update()
+{
+    for (int scheme : {S_NPOL, S_NSOL})
+        for (bool own : {true, false}) {
+            plan = FusedPlan{8, 0, 64, own};
+            Sim a(scheme);
+            long t = 0;
+            auto step = [&](int n, bool in_place) {
+                const int before = dev.singles;
+                lbm_step(a.c, n);
+                t += n;
+                expect((dev.singles > before) == in_place, NAMES[scheme] + std::string(" route of update ") + std::to_string(t));
+                expect(a.count() == t, NAMES[scheme] + std::string(" state"));
+            };
+            for (int k = 0; k < 3; ++k) {
+                step(1, own && k == 0);
+                step(1, own);
+                step(1, own);
+                step(10, false);
+            }
+        }
+}
+
 // Memory held for several updates per launch goes back when an allocation
 // fails, but nothing that a captured call refers to.
 void given_back()
@@ -385,6 +410,7 @@ const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_load", captured_load},
     {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
+    {"calls_of_one_update", calls_of_one_update},
     {"given_back", given_back},
     {"given_back_to_others", given_back_to_others},
     {"given_back_across_threads", given_back_across_threads},

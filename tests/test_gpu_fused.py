@@ -93,6 +93,15 @@ def test_one_lattice_schemes_bitwise(nx, ny, precision):
                     assert np.array_equal(a, b, equal_nan=True), (nx, ny, xa, ya, kw, np.argwhere(a != b)[:3])
 
 
+@pytest.mark.parametrize("scheme", ["NPOL", "NSOL"])
+@pytest.mark.parametrize("nx,ny,layout,precision", [(3011, 1003, "stream", "fp32"), (700, 501, "collision", "fp16sr"),
+                                                    (2311, 701, "bundle", "fp16s"), (3001, 2501, "stream", "fp16c")])
+def test_calls_of_one_update_bitwise(nx, ny, layout, precision, scheme):
+    """Calls of one update run the scheme's own kernel on these grids (NSOL in
+    16 bits beyond 256 MB), between launches of several."""
+    _compare(nx, ny, AXES[2:3], [scheme], [layout], [precision], calls=(1, 1, 8, 1, 1, 1, 6, 1))
+
+
 @pytest.mark.parametrize("scheme", ["NPTL", "PUSH", "AA", "NPOL", "NSOL"])
 def test_captured_steps_replay(scheme):
     """A captured call of an even number of updates can be replayed, with eager
