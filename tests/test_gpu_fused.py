@@ -62,6 +62,26 @@ def test_large_grid_layouts_bitwise():
     _compare(3011, 1003, AXES[1:4], ["NPTL", "PUSH", "AA", "NSOL"], ["stream"], ["fp32"], calls=(16, 13))
 
 
+# 16-bit formats on grids of several updates per launch in strips (checked
+# without a GPU in test_plans_cpu.py): nx, ny, precision, schemes, layouts.
+# FP16C in NPTL and in stream AA and PUSH has them beyond 256 MB of lattices,
+# the FP16S-SR pull of NPTL beyond 2.4 million nodes.
+STRIPS_16_BIT = [
+    (2311, 701, "fp16c", ["PUSH", "AA"], ["bundle", "collision"]),
+    (2311, 701, "fp16csr", ["PUSH", "AA", "LPTL"], ["bundle", "collision"]),
+    (2311, 701, "fp16sr", ["PUSH", "AA", "LPTL"], ["stream", "collision"]),
+    (2311, 701, "fp16c", ["LPTL"], ["stream", "bundle"]),
+    (3011, 1003, "fp16sr", ["NPTL"], ["stream", "bundle"]),
+    (3011, 2515, "fp16c", ["NPTL", "AA", "PUSH"], ["stream"]),
+    (3011, 2515, "fp16csr", ["NPTL", "AA", "PUSH"], ["stream"]),
+]
+
+
+@pytest.mark.parametrize("nx,ny,precision,schemes,layouts", STRIPS_16_BIT)
+def test_16_bit_strips_bitwise(nx, ny, precision, schemes, layouts):
+    _compare(nx, ny, AXES[2:3], schemes, layouts, [precision], calls=(8, 5))
+
+
 @pytest.mark.parametrize("precision", ALL_PRECISIONS)
 @pytest.mark.parametrize("nx,ny", [(128, 64), (37, 20), (5, 3), (57, 5), (200, 101), (2311, 701), (200003, 9), (13, 125003)])
 def test_one_lattice_schemes_bitwise(nx, ny, precision):

@@ -1,0 +1,49 @@
+"""Which grids do several updates per launch: the grids of the bitwise tests
+have to be among them, or those would compare single updates with themselves.
+The plan is asked of the built library; no GPU is needed.
+"""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from oracle import CLOSED, INFLOW_OUTFLOW
+from paper_2607_20650_amd import lbm
+from tests.test_gpu_fused import STRIPS_16_BIT
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def plan_of(tmp_path_factory):
+    if not os.path.exists(lbm.LIB_PATH):
+        pytest.skip("library not built")
+    lbm.load_library()
+    so = str(tmp_path_factory.mktemp("plan") / "plan.so")
+    model = os.path.join(HERE, "host_model")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", model,
+                    "-I", os.path.join(ROOT, "paper_2607_20650_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
+                    os.path.join(model, "plan.cpp"), lbm.LIB_PATH, "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+
+    def ask(nx, ny, scheme, layout, precision):
+        grid = lbm.Grid(nx, ny, lbm.SCHEMES[scheme], lbm.LAYOUTS[layout], lbm.PRECISIONS[precision], 0, 0)
+        bc = lbm.BC(INFLOW_OUTFLOW, CLOSED, (ctypes.c_double * 2)(), (ctypes.c_double * 2)(), 1.0,
+                    (ctypes.c_double * 2)(), 0)
+        flags = np.zeros((ny, nx), np.uint8)
+        out = (ctypes.c_int32 * 4)()
+        assert lib.plan_of(ctypes.byref(grid), ctypes.byref(bc), flags.ctypes.data_as(ctypes.c_void_p), out) == 0
+        return dict(kk=out[0], tile=out[1], rows=out[2], own=out[3])
+
+    return ask
+
+
+@pytest.mark.parametrize("nx,ny,precision,schemes,layouts", STRIPS_16_BIT)
+def test_16_bit_grids_run_in_strips(plan_of, nx, ny, precision, schemes, layouts):
+    for scheme in schemes:
+        for layout in layouts:
+            q = plan_of(nx, ny, scheme, layout, precision)
+            assert q["kk"] > 1 and not q["tile"], (scheme, layout, q)
