@@ -262,10 +262,16 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // so short that the rows recomputed for eight cost more than two launches
     // less (6000 x 400 bundle: 10.6 against 11.2 us per update, alone 14.4
     // against 17.6; 1000 x 2600: 12.8, 13.5; 4096 x 1024: 17.3, 16.7).
-    // The FP16S-SR pull spends most on its codec: three, on 1280 blocks (4096 x
-    // 1024 alone 29.6 against 31.6 us, beside two others 22.4 against 22.0;
-    // single updates, which run in the 256 MB cache alone, 27 and 43).
+    // The FP16S-SR pull spends most on its codec: three, on 1280 blocks.  Beside
+    // the fast single updates of NPTL (stream, bundle) that is no gain for a
+    // simulation alone, whose lattices stay in the cache, and a large one for
+    // several on streams of their own, whose lattices do not (per update alone,
+    // and of each of three side by side, strips against single updates: 1300 x
+    // 1300 17.6 : 13.8, 13.1 : 13.1; 2048 x 1024 17.2 : 16.0, 13.8 : 13.4; 2500 x
+    // 1100 21.8 : 21.8, 17.5 : 29.4; 4096 x 1024 29.8 : 29.5, 22.2 : 37.6).  So
+    // from the size on where three no longer fit it together.
     const bool push = scheme == S_PUSH || scheme == S_AA, sr = prec == P_FP16SR && !push;
+    if (sr && scheme == S_NPTL && layout != L_COLLISION && g.nx * g.ny <= 2400000) return FusedPlan{};
     const int most = sr                ? 3
                      : prec != P_FP32  ? fused_most<uint16_t>()
                      : g.nx * g.ny <= 3000000 ? 6

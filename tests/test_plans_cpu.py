@@ -47,3 +47,8 @@ def test_16_bit_grids_run_in_strips(plan_of, nx, ny, precision, schemes, layouts
         for layout in layouts:
             q = plan_of(nx, ny, scheme, layout, precision)
             assert q["kk"] > 1 and not q["tile"], (scheme, layout, q)
+
+
+@pytest.mark.parametrize("nx,ny,several", [(1000, 601, True), (1300, 1300, False), (2048, 1024, False), (4096, 1024, True)])
+def test_fp16s_sr_pull_keeps_single_updates_where_they_are_faster(plan_of, nx, ny, several):
+    assert (plan_of(nx, ny, "NPTL", "stream", "fp16sr")["kk"] > 1) == several
