@@ -279,7 +279,7 @@ lbm_status lbm3_create(const lbm3_grid* grid, const uint8_t* flags, double tau, 
     // neighbours' types) and, for several updates per launch of AA, a second
     // lattice
     if (grid->layout != LBM_COLLISION) (void)alloc_spare3(c, (void**)&c->links, c->link_bytes());
-    c->several = c->links && fused3_serves(g, grid->layout, grid->precision);
+    c->several = c->links && fused3_serves(g, grid->scheme, grid->layout, grid->precision);
     if (c->several && grid->scheme == LBM_AA)
         c->several = lat_bytes <= SPARE_MOST && alloc_spare3(c, &c->lat[1], lat_bytes);
     c->kp.links = c->links;

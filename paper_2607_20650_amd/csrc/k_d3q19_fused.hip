@@ -347,22 +347,40 @@ hipError_t launch3_links(const Geometry3& g, const uint8_t* types, uint32_t* lin
     return hipGetLastError();
 }
 
-bool fused3_serves(const Geometry3& g, int layout, int prec)
+bool fused3_serves(const Geometry3& g, int scheme, int layout, int prec)
 {
     // While the lattices stay in the cache, single updates hold out: a block's
-    // planes come one after another, and small grids leave CUs without a block
-    // (per update with two simulations beside / alone, FP32 pull: 128 x 96 x 96
-    // duct 41 / 41 us against 37 / 39 here, 100 x 60 x 80 18 / 24, 18 / 23; 201 x
-    // 97 x 85 65 / 64, 49 / 51).  16-bit storage makes two updates per launch
-    // bound by its codec: it gains where the x axis is not periodic, so that two
-    // of a row's few wavefronts hold boundary nodes in single updates, from 2
-    // million nodes on (FP16S, AA: 160 x 130 x 128 86 / 73 against 61 / 70), the
-    // costlier formats from 4 (FP16S-SR pull: 160 x 130 x 128 70 / 64 against 74 /
-    // 82, 230 x 140 x 200 181 / 181 against 143 / 156); 256^3 all periodic FP16S
-    // 258 against 322 alone.  The kernel's byte offsets within a plane stay below
-    // OFF_NONE.  The collision layout keeps its staged kernels: a wavefront's
-    // load of one direction is not one run there.
-    if (prec != P_FP32 && g.xa == AX_PERIODIC) return false;
+    // planes come one after another, and small grids leave CUs without a block.
+    // FP32 from 1.5 million nodes on, where duct and periodic box, pull and AA
+    // gain (us per update here : single updates, alone, and of each of three side
+    // by side; pull in the stream layout, then AA: 201 x 97 x 85 duct 49 : 63, 46
+    // : 64 and 54 : 55, 52 : 66, box 44 : 60, 48 : 59 and 46 : 51, 50 : 58).
+    // Below, some lose what others gain: 128 x 112 x 100 duct 45 : 47, 41 : 50 and
+    // 48 : 42, 46 : 49, box 43 : 44, 42 : 42 and 46 : 35, 45 : 38; 128 x 96 x 96
+    // duct 38 : 41, 35 : 41 and 40 : 36, 38 : 44, box 36 : 39, 37 : 36 and 39 : 30,
+    // 39 : 34.
+    // Periodic rows of 64 nodes stay with single updates at any size, and those of
+    // 128 but for the stream pull: they fill whole wavefronts there, and 60 columns
+    // kept of 64 make two strips of 64, three of 128 (box; pull in the stream
+    // layout, in the blocked one, then AA: 64 x 160 x 160 54 : 48, 49 : 46 and 51 :
+    // 44, 49 : 44 and 56 : 39, 53 : 45; 64 x 256 x 256 135 : 120, 118 : 123 and 123
+    // : 111, 112 : 112 and 145 : 110, 127 : 123; 128^3 68 : 68, 61 : 69 and 63 : 55,
+    // 57 : 57 and 72 : 51, 65 : 65).  With an inlet and an outlet two wavefronts of
+    // such a row take the boundary path, and beside others most gain (128^3 duct 66
+    // : 68, 62 : 82 and 64 : 60, 59 : 71 and 72 : 60, 64 : 77).
+    // 16-bit storage makes two updates per launch bound by its codec: it gains
+    // where the x axis is not periodic, so that two of a row's few wavefronts hold
+    // boundary nodes in single updates, from 2 million nodes on (FP16S, AA: 160 x
+    // 130 x 128 86 / 73 against 61 / 70), the costlier formats from 4 (FP16S-SR
+    // pull: 160 x 130 x 128 70 / 64 against 74 / 82, 230 x 140 x 200 181 / 181
+    // against 143 / 156); 256^3 all periodic FP16S 258 against 322 alone.
+    // The kernel's byte offsets within a plane stay below OFF_NONE.  The
+    // collision layout keeps its staged kernels: a wavefront's load of one
+    // direction is not one run there.
+    if (g.xa == AX_PERIODIC) {
+        const bool stream_pull = scheme != S_AA && layout == L_STREAM;
+        if (prec != P_FP32 || g.nx == 64 || (g.nx == 128 && !stream_pull)) return false;
+    }
     const int64_t least = prec == P_FP32 ? 1500000 : prec == P_FP16S ? 2000000 : 4000000;
     const int64_t plane = (layout == L_BLOCKED ? g.pstep : g.plane) * (prec == P_FP32 ? 4 : 2);
     return layout != L_COLLISION && g.nx * g.ny * g.nz >= least && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
@@ -371,7 +389,7 @@ bool fused3_serves(const Geometry3& g, int layout, int prec)
 
 hipError_t launch3_fused(int scheme, int layout, int prec, const KParams3& p, const void* src, void* dst, hipStream_t s)
 {
-    if (!p.links || !fused3_serves(p.g, layout, prec)) return hipErrorInvalidValue;
+    if (!p.links || !fused3_serves(p.g, scheme, layout, prec)) return hipErrorInvalidValue;
     const Geometry3& g = p.g;
     const int64_t strips = (g.nx + KEPT3_X - 1) / KEPT3_X, tiles = strips * ((g.ny + KEPT3_Y - 1) / KEPT3_Y);
     // Chunks of planes: rounds of 256 blocks, one per CU, times the planes a

@@ -23,7 +23,7 @@ hipError_t launch3_update(int scheme, int layout, int prec, const KParams3& p, i
                           void* obuf, hipStream_t s);
 
 // Whether launch3_fused serves a grid, and where it is the faster path.
-bool fused3_serves(const Geometry3& g, int layout, int prec);
+bool fused3_serves(const Geometry3& g, int scheme, int layout, int prec);
 hipError_t launch3_links(const Geometry3& g, const uint8_t* types, uint32_t* links, hipStream_t s);
 // FUSED3 updates in one launch, src -> dst; AA: from an even update count.
 hipError_t launch3_fused(int scheme, int layout, int prec, const KParams3& p, const void* src, void* dst, hipStream_t s);

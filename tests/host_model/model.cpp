@@ -361,7 +361,7 @@ hipError_t launch3_update(int scheme, int, int, const KParams3& p, int parity, c
             write(dst, read(src, ST_PULL) + 1, ST_PULL);
     });
 }
-bool fused3_serves(const Geometry3&, int, int) { return serves3; }
+bool fused3_serves(const Geometry3&, int, int, int) { return serves3; }
 hipError_t launch3_fused(int scheme, int, int, const KParams3& p, const void* src, void* dst, hipStream_t s)
 {
     const void* links = p.links;

@@ -1,6 +1,8 @@
-// The plan of a grid (fused_plan of the built library), for test_plans_cpu.py.
+// The plans of grids (fused_plan, fused3_serves of the built library), for
+// test_plans_cpu.py.
 #include <string>
 
+#include "lbm3_kernels.hpp"
 #include "lbm_host.hpp"
 #include "lbm_kernels.hpp"
 
@@ -15,4 +17,17 @@ extern "C" int plan_of(const lbm_grid* grid, const lbm_bc* bc, const uint8_t* fl
     out[2] = q.rows;
     out[3] = q.own;
     return 0;
+}
+
+extern "C" int serves3_of(int64_t nx, int64_t ny, int64_t nz, int xa, int scheme, int layout)
+{
+    lbm::Geometry3 g{};
+    g.nx = nx;
+    g.ny = ny;
+    g.nz = nz;
+    g.px = (nx + 15) / 16 * 16;
+    g.plane = g.px * ny;
+    g.xa = xa;
+    g.ya = g.za = lbm::AX_CLOSED;
+    return lbm::fused3_serves(g, scheme, layout, lbm::P_FP32);
 }

@@ -9,7 +9,7 @@ import subprocess
 import numpy as np
 import pytest
 
-from oracle import CLOSED, INFLOW_OUTFLOW
+from oracle import CLOSED, INFLOW_OUTFLOW, PERIODIC
 from paper_2607_20650_amd import lbm
 from tests.test_gpu_fused import STRIPS_16_BIT
 
@@ -18,7 +18,7 @@ ROOT = os.path.dirname(HERE)
 
 
 @pytest.fixture(scope="module")
-def plan_of(tmp_path_factory):
+def plans(tmp_path_factory):
     if not os.path.exists(lbm.LIB_PATH):
         pytest.skip("library not built")
     lbm.load_library()
@@ -27,15 +27,18 @@ def plan_of(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", model,
                     "-I", os.path.join(ROOT, "paper_2607_20650_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
                     os.path.join(model, "plan.cpp"), lbm.LIB_PATH, "-o", so], check=True)
-    lib = ctypes.CDLL(so)
+    return ctypes.CDLL(so)
 
+
+@pytest.fixture(scope="module")
+def plan_of(plans):
     def ask(nx, ny, scheme, layout, precision):
         grid = lbm.Grid(nx, ny, lbm.SCHEMES[scheme], lbm.LAYOUTS[layout], lbm.PRECISIONS[precision], 0, 0)
         bc = lbm.BC(INFLOW_OUTFLOW, CLOSED, (ctypes.c_double * 2)(), (ctypes.c_double * 2)(), 1.0,
                     (ctypes.c_double * 2)(), 0)
         flags = np.zeros((ny, nx), np.uint8)
         out = (ctypes.c_int32 * 4)()
-        assert lib.plan_of(ctypes.byref(grid), ctypes.byref(bc), flags.ctypes.data_as(ctypes.c_void_p), out) == 0
+        assert plans.plan_of(ctypes.byref(grid), ctypes.byref(bc), flags.ctypes.data_as(ctypes.c_void_p), out) == 0
         return dict(kk=out[0], tile=out[1], rows=out[2], own=out[3])
 
     return ask
@@ -52,3 +55,15 @@ def test_16_bit_grids_run_in_strips(plan_of, nx, ny, precision, schemes, layouts
 @pytest.mark.parametrize("nx,ny,several", [(1000, 601, True), (1300, 1300, False), (2048, 1024, False), (4096, 1024, True)])
 def test_fp16s_sr_pull_keeps_single_updates_where_they_are_faster(plan_of, nx, ny, several):
     assert (plan_of(nx, ny, "NPTL", "stream", "fp16sr")["kk"] > 1) == several
+
+
+@pytest.mark.parametrize("scheme,layout", [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "stream")])
+@pytest.mark.parametrize("nx,ny,nz,axis,several", [
+    (201, 97, 85, PERIODIC, True), (201, 97, 85, INFLOW_OUTFLOW, True), (128, 96, 96, INFLOW_OUTFLOW, False),
+    (128, 128, 128, PERIODIC, None), (64, 256, 256, PERIODIC, False), (128, 128, 128, INFLOW_OUTFLOW, True),
+    (256, 256, 256, PERIODIC, True)])
+def test_two_d3q19_updates_per_launch_where_they_are_faster(plans, nx, ny, nz, axis, several, scheme, layout):
+    if several is None:
+        several = (scheme, layout) == ("NPTL", "stream")
+    i64 = ctypes.c_int64
+    assert plans.serves3_of(i64(nx), i64(ny), i64(nz), axis, lbm.SCHEMES[scheme], lbm.LAYOUTS[layout]) == several
