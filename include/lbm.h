@@ -26,6 +26,11 @@
  *     on_device != 0 (they must then be device pointers valid on the context's
  *     device and stream), else they are host pointers and the call
  *     synchronizes the stream before returning.
+ *   - Calls on a stream under HIP graph capture are recorded with the state's
+ *     present place and may be replayed while the number of updates since is
+ *     even.  For that, from the first captured call on a context does one update
+ *     per launch, captured or not (lbm_set_bundle).  Calls that synchronize or
+ *     allocate (host arrays, lbm_diag) cannot be captured.
  *   - Spare memory: a one-lattice scheme also allocates a second lattice, while
  *     one takes at most 1.5 GiB, to do several updates per launch, and a D3Q19
  *     simulation in the stream or blocked layout 4 bytes per node that spare its
@@ -167,8 +172,8 @@ typedef struct lbm_ctx lbm_ctx;
 lbm_status lbm_create(const lbm_grid* grid, const uint8_t* flags, double tau, const lbm_bc* bc, void* stream,
                       lbm_ctx** out);
 
-/* lbm_step -- enqueue n >= 0 lattice updates (Eq. 1; streaming per scheme).
- * Asynchronous; consecutive calls replay cached HIP graphs of K updates. */
+/* lbm_step -- enqueue n >= 0 lattice updates (Eq. 1; streaming per scheme), as
+ * lbm_set_bundle describes.  Asynchronous. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t n);
 
 /*
@@ -233,17 +238,18 @@ typedef struct {
     int32_t scheme, layout, precision;
     int32_t tile_x, tile_y;  /* tile chosen for tiled schemes (0 for LPTL) */
     int32_t block;           /* threads per block of the update kernel */
-    int32_t bundle;          /* updates per cached HIP graph (0 = no graphs) */
+    int32_t bundle;          /* as set by lbm_set_bundle */
     int64_t device_bytes;    /* device memory owned by the context, spare memory included */
     int64_t fluid_nodes;     /* fluid + outlet nodes */
 } lbm_info;
 
 lbm_status lbm_get_info(const lbm_ctx* ctx, lbm_info* info);
 
-/* lbm_set_bundle -- updates per cached HIP graph used by lbm_step; a launch does
- * as many of them as suit the grid (the result is bitwise that of single
- * updates), and bundles of four launches or fewer are launched directly.  0 = one launch of the scheme's own kernel per update, no graph.
- * Default 32. */
+/* lbm_set_bundle -- the largest unit in which lbm_step enqueues updates.  A
+ * launch does as many updates as suit the grid (the result is bitwise that of
+ * single ones); units of more than four launches are replayed as cached HIP
+ * graphs, smaller ones and what is left of a call are launched directly.
+ * 0 = one launch of the scheme's own kernel per update, no graph.  Default 32. */
 lbm_status lbm_set_bundle(lbm_ctx* ctx, int32_t k);
 
 /* lbm_sync -- wait for all work enqueued on the context's stream. */

@@ -86,9 +86,10 @@ struct lbm_ctx final : SpareOwner {
     bool load_captured = false; // of lbm_set_state
     int32_t bundle = 32;
     int32_t block = 256;
-    hipGraph_t graph[4] = {}; // by graph_key
-    hipGraphExec_t gexec[4] = {};
-    int graph_cur[4] = {}; // the lattice that holds the state after each graph
+    static constexpr int GRAPHS = 8;
+    hipGraph_t graph[GRAPHS] = {}; // by graph_key
+    hipGraphExec_t gexec[GRAPHS] = {};
+    int graph_cur[GRAPHS] = {}; // the lattice that holds the state after each graph
     bool have_prev = false;
     bool poisoned = false;
     std::string err;
@@ -131,7 +132,7 @@ namespace {
 
 void drop_graphs(lbm_ctx* c)
 {
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < lbm_ctx::GRAPHS; ++k) {
         if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
         if (c->graph[k]) (void)hipGraphDestroy(c->graph[k]);
         c->gexec[k] = nullptr;
@@ -330,8 +331,12 @@ lbm_status launch_updates(lbm_ctx* c, int64_t t, int64_t n, int most, int& cur, 
 
 // Which cached graph serves the next bundle: a graph holds the lattices it was
 // captured with and, with one lattice or a Neumann inlet, starts at one update
-// parity (elsewhere the parity follows the lattice or does not matter).
-int graph_key(const lbm_ctx* c) { return c->cur * 2 + (is_two_lattice(c->grid.scheme) ? 0 : (int)(c->t & 1)); }
+// parity (elsewhere the parity follows the lattice or does not matter).  Those
+// from before the first captured call may do several updates per launch.
+int graph_key(const lbm_ctx* c)
+{
+    return c->captured * 4 + c->cur * 2 + (is_two_lattice(c->grid.scheme) ? 0 : (int)(c->t & 1));
+}
 
 lbm_status build_graph(lbm_ctx* c, int key)
 {
@@ -358,17 +363,18 @@ lbm_status build_graph(lbm_ctx* c, int key)
     return LBM_OK;
 }
 
-// Before a call that records the address of a lattice: a captured one is
-// replayed with the lattices it was captured with, so from the first one on
-// the context does single updates, which leave the state where they found it
-// after every even number, and bundles by direct launch.  (Several updates per
+// Before a call that records the address of a lattice; whether it is being
+// captured.  A captured call is replayed with the lattices it was captured
+// with, so from the first one on the context does single updates, which leave
+// the state where they found it after every even number.  (Several updates per
 // launch leave it in either lattice, by the number of launches: a readout
 // captured before 100 updates of AA, in 13 launches, would read the other one.)
-void watch_capture(lbm_ctx* c)
+bool watch_capture(lbm_ctx* c)
 {
-    if (c->plan.kk == 1 || !capturing(c->stream)) return;
+    if (!capturing(c->stream)) return false;
     c->captured = true;
     c->plan = FusedPlan{};
+    return true;
 }
 
 lbm_status ensure_readout(lbm_ctx* c)
@@ -663,7 +669,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    watch_capture(c);
+    const bool capture = watch_capture(c);
     // One update where the scheme's own kernel is the faster one: not right
     // after launches of several, when its edge buffers would have to be refilled
     // (calls of 8 and 1 updates in turn on 4096 x 1024 NPOL FP32: 27 us per
@@ -678,13 +684,13 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n)
         const hipError_t e = launch_edge_fill(c->state, c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                                               c->edge[c->t & 1], c->stream);
         if (e != hipSuccess) return c->check(e, "edge fill");
-        c->edges_old = capturing(c->stream);
+        c->edges_old = capture;
     }
     // A graph of few launches costs the host more than they do: 128 x 64, 200
     // updates as 6 graphs of 3 launches and one more 207 us, as 17 launches
     // 171; graphs of 8 launches save up to 40 % beside other simulations (513 x
     // 257, 96 updates: 100 against 117 - 142 us).
-    const bool graphs = !c->captured && c->bundle > 4 * (int64_t)most;
+    const bool graphs = !capture && c->bundle > 4 * (int64_t)most;
     while (graphs && n >= c->bundle) {
         const int key = graph_key(c);
         if (!c->gexec[key]) {
@@ -733,7 +739,7 @@ lbm_status lbm_macros(lbm_ctx* c, float* rho, float* u, int on_device)
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (!rho && !u) return LBM_OK;
-    watch_capture(c);
+    (void)watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     if (on_device) {
         return c->check(launch_macros(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), rho, u,
@@ -756,7 +762,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, float* f, int on_device)
     if (!c || !f) return LBM_EINVAL;
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
-    watch_capture(c);
+    (void)watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     if (on_device)
         return c->check(launch_get_populations(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), f,
@@ -776,7 +782,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     if (!c || !f) return LBM_EINVAL;
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
-    watch_capture(c);
+    const bool capture = watch_capture(c);
     const int64_t N = c->grid.nx * c->grid.ny;
     const float* src = f;
     if (!on_device) {
@@ -788,7 +794,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     }
     // the push state is built from the pull form through a second lattice;
     // AA, which has one, borrows a temporary one
-    if (c->captured && capturing(c->stream)) c->load_captured = true;
+    if (capture) c->load_captured = true;
     void* tmp = c->other_lat();
     const bool borrow = c->state_now() == ST_PUSH && !tmp;
     if (borrow && device_alloc(&tmp, (size_t)c->lat_elems * c->elem, c) != hipSuccess)
@@ -801,7 +807,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const float* f, int on_device)
     if (e == hipSuccess && c->edge_elems)
         e = launch_edge_fill(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(),
                              c->edge[c->t & 1], c->stream);
-    c->edges_old = c->edges_old && capturing(c->stream);
+    c->edges_old = c->edges_old && capture;
     if (e == hipSuccess && c->obuf && c->state_now() == ST_SWAP)
         e = launch_aa_outlet_fill(c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), c->obuf, c->stream);
     if (borrow) {
@@ -863,7 +869,7 @@ lbm_status lbm_diag_noalloc(lbm_ctx* c, double* u_prev, int32_t have_prev, doubl
     double* scr = nullptr;
     lbm_status st = noalloc_scratch(c, &scr);
     if (st != LBM_OK) return st;
-    watch_capture(c);
+    (void)watch_capture(c);
     double* sums = scr + diag_partials(); // 5 sums after the partials
     hipError_t e = launch_diag(c->state_now(), c->grid.layout, c->grid.precision, c->view(), c->cur_lat(), u_prev,
                                have_prev ? 1 : 0, scr, sums, c->stream);

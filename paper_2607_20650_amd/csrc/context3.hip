@@ -113,15 +113,16 @@ bool alloc_spare3(lbm3_ctx* c, void** p, size_t bytes)
     return false;
 }
 
-// Before a call that records the address of a lattice: a captured one is
-// replayed with the lattices it was captured with, so from the first one on
-// the context does single updates, which leave the state where they found it
-// after every even number.
-void watch_capture3(lbm3_ctx* c)
+// Before a call that records the address of a lattice; whether it is being
+// captured.  A captured call is replayed with the lattices it was captured
+// with, so from the first one on the context does single updates, which leave
+// the state where they found it after every even number.
+bool watch_capture3(lbm3_ctx* c)
 {
-    if (c->captured || !capturing(c->stream)) return;
+    if (!capturing(c->stream)) return false;
     c->captured = true;
     c->several = false;
+    return true;
 }
 
 lbm_status ensure_readout3(lbm3_ctx* c)
@@ -308,7 +309,7 @@ lbm_status lbm3_step(lbm3_ctx* c, int64_t n)
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
     if (n < 0) return c->fail(LBM_EINVAL, "negative step count");
-    watch_capture3(c);
+    (void)watch_capture3(c);
     while (n > 0) {
         const int parity = (int)(c->t & 1);
         void* const src = c->lat[c->now];
@@ -339,7 +340,7 @@ lbm_status lbm3_macros(lbm3_ctx* c, float* rho, float* u, int on_device)
     if (!c) return LBM_EINVAL;
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
-    watch_capture3(c);
+    (void)watch_capture3(c);
     if (on_device)
         return c->check(launch3_macros(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(), rho, u,
                                        c->stream),
@@ -361,7 +362,7 @@ lbm_status lbm3_get_populations(lbm3_ctx* c, float* f, int on_device)
     if (!c || !f) return LBM_EINVAL;
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
-    watch_capture3(c);
+    (void)watch_capture3(c);
     if (on_device)
         return c->check(launch3_get_populations(c->state(), c->grid.layout, c->grid.precision, c->kp, c->cur(), f,
                                                 c->stream),
@@ -381,7 +382,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
     if (!c || !f) return LBM_EINVAL;
     const std::lock_guard<std::mutex> call(c->mu);
     if (c->poisoned) return LBM_EDEVICE;
-    watch_capture3(c);
+    const bool capture = watch_capture3(c);
     const float* src = f;
     if (!on_device) {
         lbm_status st = ensure_readout3(c);
@@ -391,7 +392,7 @@ lbm_status lbm3_set_state(lbm3_ctx* c, const float* f, int on_device)
         if (e != hipSuccess) return c->check(e, "state upload");
         src = c->readout;
     }
-    if (c->captured && capturing(c->stream)) c->load_captured = true;
+    if (capture) c->load_captured = true;
     // the push form is built from the pull form through a second lattice
     void* tmp = c->lat[c->now ^ 1];
     const bool borrow = c->state() == ST_PUSH && !tmp;

@@ -208,6 +208,37 @@ void captured_3d()
     }
 }
 
+// After a captured call bundles of single updates are replayed as cached graphs
+// again, none that was made before it, and none while the stream is captured.
+void graphs_after_capture()
+{
+    for (int scheme : SCHEMES) {
+        plan = FusedPlan{4, 1, 0};
+        const std::string name = NAMES[scheme];
+        Sim a(scheme);
+        lbm_set_bundle(a.c, 24);
+        lbm_step(a.c, 24); // six launches: a graph
+        expect(dev.graph_launches > 0, name + ": graph before");
+        const Graph g = capture(a.stream, [&] {
+            const int before = dev.graph_launches;
+            expect(lbm_step(a.c, 48) == LBM_OK && dev.graph_launches == before, name + ": no graph while captured");
+        });
+        expect(g.work.size() >= 48, name + ": single updates captured");
+        long t = 24;
+        for (int k = 0; k < 4; ++k) {
+            const int graphs = dev.graph_launches, singles = dev.singles, fused = dev.fused;
+            lbm_step(a.c, 72);
+            expect(dev.graph_launches == graphs + 3, name + ": graphs after");
+            expect(dev.singles == singles + 72 && dev.fused == fused, name + ": single updates after");
+            t += 72;
+            expect(a.count() == t, name + ": state");
+            replay(g);
+            t += 48;
+            expect(a.count() == t, name + ": state after a replay");
+        }
+    }
+}
+
 // Calls of one update of NPOL and NSOL: in place where the plan says so, but
 // not right after launches of several updates.
 void calls_of_one_update()
@@ -410,6 +441,7 @@ const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_load", captured_load},
     {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
+    {"graphs_after_capture", graphs_after_capture},
     {"calls_of_one_update", calls_of_one_update},
     {"given_back", given_back},
     {"given_back_to_others", given_back_to_others},
