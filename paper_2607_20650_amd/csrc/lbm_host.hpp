@@ -233,15 +233,16 @@ private:
 // where the transfer to pinned memory takes 385; here 680 (one thread 825: it
 // reads what the transfer left in memory; three and more the same as two), and
 // into memory not touched before 1400 instead of 2200.  The runtime's copies
-// to the device (580 us) did not gain this way.  Pinned and device memory, and
-// copies too small to gain, go straight to the runtime.
+// to the device (580 us) did not gain this way.  Pinned and device memory,
+// copies too small to gain, and those made while another device than the
+// stream's is the current one go straight to the runtime.
 class HostRing {
 public:
     // src (device) -> dst; on return the data is in dst, or the copy is
     // enqueued on s
     hipError_t to_host(void* dst, const void* src, size_t bytes, hipStream_t s)
     {
-        char* const buf = serves(dst, bytes) ? PinnedPool::get().take() : nullptr;
+        char* const buf = serves(dst, bytes, s) ? PinnedPool::get().take() : nullptr;
         if (!buf) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         const hipError_t res = segments(bytes, [=](int w, size_t lo, size_t hi) {
             const size_t chunk = chunk_of(hi - lo), n = (hi - lo + chunk - 1) / chunk;
@@ -315,9 +316,16 @@ private:
             if (e != hipSuccess) return e;
         return hipSuccess;
     }
-    bool serves(const void* host, size_t bytes)
+    bool serves(const void* host, size_t bytes, hipStream_t s)
     {
         if (bytes < LEAST || off_) return false;
+        // events have to be of the stream's device
+        hipDevice_t of = 0;
+        int dev = 0;
+        if (hipStreamGetDevice(s, &of) != hipSuccess || hipGetDevice(&dev) != hipSuccess || of != dev) {
+            (void)hipGetLastError();
+            return false;
+        }
         hipPointerAttribute_t a{};
         if (hipPointerGetAttributes(&a, host) == hipSuccess) {
             if (a.type != hipMemoryTypeUnregistered) return false;

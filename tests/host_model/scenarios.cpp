@@ -264,6 +264,29 @@ void calls_of_one_update()
         }
 }
 
+// Host readouts of a simulation while another device is the current one: the
+// first through the pinned chunks, and later ones.
+void readout_from_another_device()
+{
+    for (int first : {0, 1}) {
+        plan = FusedPlan{8, 1, 0};
+        (void)hipSetDevice(0);
+        Sim a(S_NPTL, 1024, 400);
+        std::vector<float> f(9 * 1024 * 400, 7.0f);
+        expect(lbm_set_state(a.c, f.data(), 0) == LBM_OK, "load");
+        for (int k = 0; k < 3; ++k) {
+            (void)hipSetDevice(k == 0 ? first : 1 - first);
+            expect(lbm_macros(a.c, f.data(), nullptr, 0) == LBM_OK, "readout with another device current");
+            expect(f[0] == 7.0f, "its values");
+            expect(lbm_get_populations(a.c, f.data(), 0) == LBM_OK, "populations with another device current");
+        }
+        int now = 0;
+        (void)hipGetDevice(&now);
+        expect(now == 1 - first, "the current device stays");
+        (void)hipSetDevice(0);
+    }
+}
+
 // Memory held for several updates per launch goes back when an allocation
 // fails, but nothing that a captured call refers to.
 void given_back()
@@ -442,6 +465,7 @@ const std::map<std::string, void (*)()> SCENARIOS = {
     {"eager_before_replay", eager_before_replay},
     {"captured_3d", captured_3d},
     {"graphs_after_capture", graphs_after_capture},
+    {"readout_from_another_device", readout_from_another_device},
     {"calls_of_one_update", calls_of_one_update},
     {"given_back", given_back},
     {"given_back_to_others", given_back_to_others},
