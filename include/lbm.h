@@ -287,9 +287,10 @@ int32_t lbm_bytes_per_update(int32_t precision);
  * every bundle is one replay of a captured HIP graph of `bundle_steps`
  * updates of every resident request by a persistent batched kernel, up to four
  * updates per launch (two-lattice pull, same arithmetic as lbm_step, so a
- * request's result is independent of the mix).  A request
- * stops at exactly its step count; its rho and u are then read back and its
- * memory freed.
+ * request's result is independent of the mix).  While a request with the
+ * Neumann inlet, or less than four rows and a periodic y axis, is resident, all
+ * advance by one update per launch.  A request stops at exactly its step
+ * count; its rho and u are then read back and its memory freed.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_server lbm_server;
 

@@ -125,7 +125,7 @@ struct lbm_server {
     // captured bundles per persistent grid size: the full grid (resident
     // blocks on the device) and smaller ones down to 1/32 of it, so that a
     // bundle over few work items launches few blocks; [1]: several updates per
-    // launch, [0]: one (captured when a request that needs it is resident)
+    // launch, [0]: one (each captured when a request that needs it is resident)
     static constexpr int NGRIDS = 6;
     hipGraph_t graph[2][NGRIDS] = {};
     hipGraphExec_t gexec[2][NGRIDS] = {};
@@ -342,29 +342,23 @@ int bundle_launches(const lbm_server* s, bool fused)
     return fused ? (s->K + BATCH_UPDATES - 1) / BATCH_UPDATES : s->K;
 }
 
-// Capture the bundles of one kind, one per grid size: launch k advances every
+// Capture the bundle of one kind for one grid size: launch k advances every
 // slot that has updates left.
-bool capture_bundles(lbm_server* s, bool fused)
+bool capture_bundle(lbm_server* s, bool fused, int v)
 {
-    const int blocks = batched_blocks(s->layout, s->precision, fused);
-    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
-        s->grid_blocks[fused][v] = std::max(1, blocks >> v);
-        if (s->gexec[fused][v]) continue;
-        if (hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
-        hipError_t e = hipSuccess;
-        for (int k = 0; k < bundle_launches(s, fused) && e == hipSuccess; ++k)
-            e = launch_batched(s->layout, s->precision, fused, s->d_slots, s->d_work, s->d_nwork, k,
-                               s->grid_blocks[fused][v], s->cap);
-        hipGraph_t g = nullptr;
-        const hipError_t e2 = hipStreamEndCapture(s->cap, &g);
-        if (e != hipSuccess || e2 != hipSuccess) {
-            if (g) (void)hipGraphDestroy(g);
-            return false;
-        }
-        s->graph[fused][v] = g;
-        if (hipGraphInstantiate(&s->gexec[fused][v], g, nullptr, nullptr, 0) != hipSuccess) return false;
+    if (hipStreamBeginCapture(s->cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return false;
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < bundle_launches(s, fused) && e == hipSuccess; ++k)
+        e = launch_batched(s->layout, s->precision, fused, s->d_slots, s->d_work, s->d_nwork, k,
+                           s->grid_blocks[fused][v], s->cap);
+    hipGraph_t g = nullptr;
+    const hipError_t e2 = hipStreamEndCapture(s->cap, &g);
+    if (e != hipSuccess || e2 != hipSuccess) {
+        if (g) (void)hipGraphDestroy(g);
+        return false;
     }
-    return true;
+    s->graph[fused][v] = g;
+    return hipGraphInstantiate(&s->gexec[fused][v], g, nullptr, nullptr, 0) == hipSuccess;
 }
 
 } // namespace
@@ -445,7 +439,11 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
     if (hipMemcpy(s->d_slots, s->h_slots[0], sizeof(SlotDesc) * max_slots, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(s->d_nwork, s->h_nwork[0], 2 * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
         return cleanup(LBM_EDEVICE, "descriptor upload failed");
-    if (!capture_bundles(s, true)) return cleanup(LBM_EDEVICE, "bundle capture failed");
+    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
+        for (bool fused : {false, true})
+            s->grid_blocks[fused][v] = std::max(1, batched_blocks(layout, precision, fused) >> v);
+        if (!capture_bundle(s, true, v)) return cleanup(LBM_EDEVICE, "bundle capture failed");
+    }
     *out = s;
     return LBM_OK;
 }
@@ -601,6 +599,11 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
         if (!s->flight.empty()) return finish_oldest(s, true);
         return LBM_OK;
     }
+    // the smallest grid with at least one block per work item (four strips)
+    const int32_t need = fused ? (nw + 3) / 4 : nw;
+    int v = 0;
+    while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[fused][v + 1] >= need) ++v;
+    if (!s->gexec[fused][v] && !capture_bundle(s, fused, v)) return s->fail(LBM_EDEVICE, "bundle capture failed");
     // the bundle's arena region: staged flags of the admitted requests, then
     // the results of the finishing ones
     int64_t up_bytes = 0;
@@ -632,8 +635,6 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
             o += (r->kp.g.nx * r->kp.g.ny + 15) / 16 * 16;
         }
     }
-    if (!fused && !s->gexec[0][lbm_server::NGRIDS - 1] && !capture_bundles(s, false))
-        return s->fail(LBM_EDEVICE, "bundle capture failed");
     s->h_nwork[s->stage][0] = nw;
     s->h_nwork[s->stage][1] = rows;
     hipError_t e = hipMemcpyAsync(s->d_slots, hs, sizeof(SlotDesc) * s->max_slots, hipMemcpyHostToDevice, s->stream);
@@ -641,11 +642,6 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
         e = hipMemcpyAsync(s->d_work, hw, sizeof(WorkItem) * nw, hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(s->d_nwork, s->h_nwork[s->stage], 2 * sizeof(int32_t), hipMemcpyHostToDevice, s->stream);
-    // the smallest captured grid with at least one block per work item (four
-    // strips)
-    const int32_t need = fused ? (nw + 3) / 4 : nw;
-    int v = 0;
-    while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[fused][v + 1] >= need) ++v;
     if (e == hipSuccess) e = hipGraphLaunch(s->gexec[fused][v], s->stream);
     st = s->check(e, "bundle launch");
     if (st != LBM_OK) return st;

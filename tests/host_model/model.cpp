@@ -13,6 +13,7 @@
 #include <set>
 
 #include "lbm3_kernels.hpp"
+#include "lbm_batched.hpp"
 #include "lbm_kernels.hpp"
 
 Device dev;
@@ -126,6 +127,12 @@ hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKin
             *(float*)dst = (float)cell(src).t;
     });
 }
+hipError_t hipMemcpy(void* dst, const void*, size_t, hipMemcpyKind)
+{
+    const std::lock_guard<std::recursive_mutex> lock(mu);
+    touch(dst);
+    return hipSuccess;
+}
 hipError_t hipMemsetAsync(void* dst, int, size_t, hipStream_t s)
 {
     return enqueue(s, [=] { touch(dst); });
@@ -184,6 +191,7 @@ hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st)
 hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode)
 {
     s->capture = new Graph();
+    ++dev.captures;
     return hipSuccess;
 }
 hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t* g)
@@ -230,6 +238,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
     return e->device == s->device ? hipSuccess : done(hipErrorInvalidHandle);
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
 
 // ------------------------------------------------------------------ launches
 namespace lbm {
@@ -337,6 +346,12 @@ hipError_t launch_diag_result(const double* sums, int, double* out, hipStream_t 
     return enqueue(s, [=] { cell(out).t = cell(sums).t; });
 }
 hipError_t launch_probe(int, void*, const void*, int64_t, hipStream_t) { return hipSuccess; }
+
+hipError_t launch_batched(int, int, bool fused, const SlotDesc*, const WorkItem*, const int32_t*, int, int, hipStream_t s)
+{
+    return enqueue(s, [=] { ++(fused ? dev.fused : dev.singles); });
+}
+int batched_blocks(int, int, bool) { return 1024; }
 
 hipError_t launch3_types(const Geometry3&, const uint8_t*, uint8_t*, hipStream_t) { return hipSuccess; }
 hipError_t launch3_links(const Geometry3&, const uint8_t*, uint32_t*, hipStream_t) { return hipSuccess; }

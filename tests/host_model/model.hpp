@@ -10,7 +10,7 @@ struct Device {
     size_t total = (size_t)288 << 30, free_bytes = (size_t)288 << 30;
     size_t largest = SIZE_MAX; // larger allocations fail
     int faults = 0;            // accesses to memory that is not allocated
-    int singles = 0, fused = 0, graph_launches = 0;
+    int singles = 0, fused = 0, graph_launches = 0, captures = 0;
 };
 extern Device dev;
 extern lbm::FusedPlan plan; // what fused_plan returns

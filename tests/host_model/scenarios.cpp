@@ -287,6 +287,32 @@ void readout_from_another_device()
     }
 }
 
+// The first served request that needs single updates makes the serving loop
+// capture one bundle, not one per grid size.
+void served_single_updates()
+{
+    Stream* stream = new Stream();
+    lbm_server* s = nullptr;
+    expect(lbm_server_create(1 << 24, 4, 10, 0, 0, stream, &s) == LBM_OK, "server");
+    const std::vector<uint8_t> flags(NX * NY, 0);
+    lbm_grid g{NX, NY, S_NPTL, 0, 0, 0, 0};
+    lbm_bc bc{};
+    bc.x_axis = LBM_NEUMANN_OUTFLOW;
+    bc.y_axis = LBM_CLOSED;
+    bc.rho0 = 1.0;
+    uint64_t id = 0;
+    expect(lbm_server_submit(s, &g, flags.data(), 0.8, &bc, 25, &id) == LBM_OK, "request");
+    const int before = dev.captures;
+    for (int k = 0; k < 4; ++k) expect(lbm_server_run_bundle(s) == LBM_OK, "bundle");
+    expect(dev.singles == 30 && dev.fused == 0, "launches of three bundles, not " + std::to_string(dev.singles));
+    expect(dev.captures == before + 1, std::to_string(dev.captures - before) + " captures in the serving loop");
+    int32_t status[2], n = 0;
+    uint64_t ids[2];
+    expect(lbm_server_poll(s, ids, status, 2, &n) == LBM_OK && n == 1 && ids[0] == id, "finished");
+    lbm_server_destroy(s);
+    delete stream;
+}
+
 // Memory held for several updates per launch goes back when an allocation
 // fails, but nothing that a captured call refers to.
 void given_back()
@@ -466,6 +492,7 @@ const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_3d", captured_3d},
     {"graphs_after_capture", graphs_after_capture},
     {"readout_from_another_device", readout_from_another_device},
+    {"served_single_updates", served_single_updates},
     {"calls_of_one_update", calls_of_one_update},
     {"given_back", given_back},
     {"given_back_to_others", given_back_to_others},

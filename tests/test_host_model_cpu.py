@@ -1,7 +1,8 @@
-"""Host code of the simulation contexts on a modelled device.
+"""Host code of the simulation contexts and the serving engine on a modelled
+device.
 
-``csrc/context.hip`` and ``csrc/context3.hip`` hold no device code of their
-own, so they compile with g++ against a model of the HIP runtime
+``csrc/context.hip``, ``csrc/context3.hip`` and ``csrc/server.hip`` hold no
+kernels, so they compile with g++ against a model of the HIP runtime
 (``host_model/hip/hip_runtime.h``) and of the launches (``host_model/model.cpp``):
 device memory has addresses and every lattice holds its update count instead of
 populations.  Each scenario checks that the addresses, the order and the
@@ -23,14 +24,15 @@ CSRC = os.path.join(ROOT, "paper_2607_20650_amd", "csrc")
 def scenarios(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("host_model") / "scenarios")
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", MODEL, "-I", CSRC, "-I", os.path.join(ROOT, "include"),
-                    "-x", "c++", os.path.join(CSRC, "context.hip"), os.path.join(CSRC, "context3.hip"),
+                    "-x", "c++", os.path.join(CSRC, "context.hip"), os.path.join(CSRC, "context3.hip"), os.path.join(CSRC, "server.hip"),
                     os.path.join(MODEL, "model.cpp"), os.path.join(MODEL, "scenarios.cpp"), "-o", exe], check=True)
     return exe
 
 
 @pytest.mark.parametrize("name", ["captured_readout", "captured_load", "eager_before_replay", "captured_3d",
                                   "graphs_after_capture", "calls_of_one_update", "given_back", "given_back_to_others",
-                                  "given_back_across_threads", "spare_memory_is_bounded", "readout_from_another_device"])
+                                  "given_back_across_threads", "spare_memory_is_bounded", "readout_from_another_device",
+                                  "served_single_updates"])
 def test_scenario(scenarios, name):
     r = subprocess.run([scenarios, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[:2000]
