@@ -239,6 +239,20 @@ FusedPlan fused_plan(const KParams& p, int scheme, int layout, int prec)
     // and with two simulations beside: 1000 x 900 5.9, 4.4 against 10.1, 4.5 us
     // in strips; 1600 x 1000 8.5, 8.0 against 12.5, 7.7; 2048 x 2048 in strips
     // 24, 19).
+    // Not where most of every tile lies outside: long grids of few rows, by how
+    // well the scheme's own kernel takes them (600000 x 1 NPTL FP32 62 us per
+    // update in tiles, 19 by single updates; 100000 x 8 NPTL FP32 13, 11, FP16S 14,
+    // 10; 100000 x 6 PUSH FP32 13.5, 11.5, AA FP16C-SR 21, 15; 100000 x 4 AA FP16S
+    // 14, 14, NPOL FP32 12, 20, FP16S 14, 13; 300000 x 2 NSOL FP16S 38, 29), and
+    // columns of one or two nodes with the costly codecs (1 x 100000 FP16C-SR 23,
+    // 13).
+    const bool codec = elem == 2 && prec != P_FP16S;
+    const int few = codec || scheme == S_NPTL || scheme == S_LPTL ? 8
+                    : scheme == S_NPOL                            ? (elem == 4 ? 0 : 4)
+                    : scheme == S_NSOL                            ? (elem == 4 ? 1 : 2)
+                    : elem == 2                                   ? 2
+                                                                  : 6;
+    if (g.nx * g.ny <= 1600000 && tiles(4) > 1024 && (g.ny <= few || (codec && g.nx <= 2))) return FusedPlan{};
     if (g.nx * g.ny <= 1600000) {
         q.tile = 1;
         const int unit = scheme == S_AA ? 2 : 1; // AA's updates come in pairs

@@ -34,7 +34,7 @@ def plans(tmp_path_factory):
 def plan_of(plans):
     def ask(nx, ny, scheme, layout, precision):
         grid = lbm.Grid(nx, ny, lbm.SCHEMES[scheme], lbm.LAYOUTS[layout], lbm.PRECISIONS[precision], 0, 0)
-        bc = lbm.BC(INFLOW_OUTFLOW, CLOSED, (ctypes.c_double * 2)(), (ctypes.c_double * 2)(), 1.0,
+        bc = lbm.BC(CLOSED, CLOSED, (ctypes.c_double * 2)(), (ctypes.c_double * 2)(), 1.0,
                     (ctypes.c_double * 2)(), 0)
         flags = np.zeros((ny, nx), np.uint8)
         out = (ctypes.c_int32 * 4)()
@@ -55,6 +55,15 @@ def test_16_bit_grids_run_in_strips(plan_of, nx, ny, precision, schemes, layouts
 @pytest.mark.parametrize("nx,ny,several", [(1000, 601, True), (1300, 1300, False), (2048, 1024, False), (4096, 1024, True)])
 def test_fp16s_sr_pull_keeps_single_updates_where_they_are_faster(plan_of, nx, ny, several):
     assert (plan_of(nx, ny, "NPTL", "stream", "fp16sr")["kk"] > 1) == several
+
+
+@pytest.mark.parametrize("nx,ny,scheme,precision,several", [
+    (600000, 1, "NPTL", "fp32", False), (100000, 8, "NPTL", "fp16s", False), (20000, 3, "NPTL", "fp32", True),
+    (100000, 8, "AA", "fp16s", True), (100000, 6, "AA", "fp16csr", False), (300000, 2, "NPOL", "fp32", True),
+    (300000, 2, "NSOL", "fp16s", False), (1, 100000, "AA", "fp16csr", False), (1, 100000, "AA", "fp32", True),
+    (40000, 12, "NPTL", "fp32", True)])
+def test_long_grids_of_few_rows(plan_of, nx, ny, scheme, precision, several):
+    assert (plan_of(nx, ny, scheme, "stream", precision)["kk"] > 1) == several
 
 
 @pytest.mark.parametrize("scheme,layout", [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "stream")])
