@@ -359,15 +359,25 @@ bool fused3_serves(const Geometry3& g, int scheme, int layout, int prec)
     // 48 : 42, 46 : 49, box 43 : 44, 42 : 42 and 46 : 35, 45 : 38; 128 x 96 x 96
     // duct 38 : 41, 35 : 41 and 40 : 36, 38 : 44, box 36 : 39, 37 : 36 and 39 : 30,
     // 39 : 34.
-    // Periodic rows of 64 nodes stay with single updates at any size, and those of
-    // 128 but for the stream pull: they fill whole wavefronts there, and 60 columns
-    // kept of 64 make two strips of 64, three of 128 (box; pull in the stream
-    // layout, in the blocked one, then AA: 64 x 160 x 160 54 : 48, 49 : 46 and 51 :
-    // 44, 49 : 44 and 56 : 39, 53 : 45; 64 x 256 x 256 135 : 120, 118 : 123 and 123
-    // : 111, 112 : 112 and 145 : 110, 127 : 123; 128^3 68 : 68, 61 : 69 and 63 : 55,
-    // 57 : 57 and 72 : 51, 65 : 65).  With an inlet and an outlet two wavefronts of
-    // such a row take the boundary path, and beside others most gain (128^3 duct 66
-    // : 68, 62 : 82 and 64 : 60, 59 : 71 and 72 : 60, 64 : 77).
+    // Grids that leave most of every tile, or of a chunk's planes with the four
+    // around it, outside stay with single updates: fewer than 6 rows (as above:
+    // 1250 x 1 x 1250 box 136 : 49, 133 : 47 and 139 : 41, 136 : 46; 700 x 4 x 600
+    // duct 63 : 53, 59 : 53 and 69 : 45, 62 : 52; 500 x 8 x 420 46 : 53, 45 : 54
+    // and 48 : 45, 49 : 53), fewer than 3 planes (900 x 900 x 2 box 66 : 56, 66 :
+    // 55 and 68 : 46, 68 : 51; 900 x 600 x 3 51 : 56, 53 : 56 and 53 : 45, 56 : 50)
+    // and, in the stream layout, rows of fewer than 24 nodes (16 x 320 x 320 box
+    // 101 : 48, 108 : 46 and 108 : 40, 119 : 48; 24 x 300 x 250 93 : 94, 92 : 126
+    // and 100 : 91, 98 : 100); the blocked layout pads such rows for both.
+    // Periodic rows of 32 or 64 nodes stay with single updates at any size, and
+    // those of 128 but for the stream pull: they fill whole wavefronts there, and
+    // 60 columns kept of 64 make two strips of 64, three of 128 (box; pull in the
+    // stream layout, in the blocked one, then AA: 32 x 256 x 256 70 : 63, 68 : 62
+    // and 69 : 60, 69 : 60 and 75 : 50, 74 : 65; 64 x 160 x 160 54 : 48, 49 : 46
+    // and 51 : 44, 49 : 44 and 56 : 39, 53 : 45; 64 x 256 x 256 135 : 120, 118 :
+    // 123 and 123 : 111, 112 : 112 and 145 : 110, 127 : 123; 128^3 68 : 68, 61 : 69
+    // and 63 : 55, 57 : 57 and 72 : 51, 65 : 65).  With an inlet and an outlet two
+    // wavefronts of such a row take the boundary path, and beside others most gain
+    // (128^3 duct 66 : 68, 62 : 82 and 64 : 60, 59 : 71 and 72 : 60, 64 : 77).
     // 16-bit storage makes two updates per launch bound by its codec: it gains
     // where the x axis is not periodic, so that two of a row's few wavefronts hold
     // boundary nodes in single updates, from 2 million nodes on (FP16S, AA: 160 x
@@ -377,14 +387,15 @@ bool fused3_serves(const Geometry3& g, int scheme, int layout, int prec)
     // The kernel's byte offsets within a plane stay below OFF_NONE.  The
     // collision layout keeps its staged kernels: a wavefront's load of one
     // direction is not one run there.
+    static_assert(FUSED3 <= 3, "a block's planes wrap around a periodic z axis once");
+    if (g.ny < 6 || g.nz < 3 || (layout == L_STREAM && g.nx < 24)) return false;
     if (g.xa == AX_PERIODIC) {
         const bool stream_pull = scheme != S_AA && layout == L_STREAM;
-        if (prec != P_FP32 || g.nx == 64 || (g.nx == 128 && !stream_pull)) return false;
+        if (prec != P_FP32 || g.nx == 32 || g.nx == 64 || (g.nx == 128 && !stream_pull)) return false;
     }
     const int64_t least = prec == P_FP32 ? 1500000 : prec == P_FP16S ? 2000000 : 4000000;
     const int64_t plane = (layout == L_BLOCKED ? g.pstep : g.plane) * (prec == P_FP32 ? 4 : 2);
-    return layout != L_COLLISION && g.nx * g.ny * g.nz >= least && (g.za != AX_PERIODIC || g.nz >= FUSED3) &&
-           plane < ((int64_t)1 << 30) && g.plane < ((int64_t)1 << 28);
+    return layout != L_COLLISION && g.nx * g.ny * g.nz >= least && plane < ((int64_t)1 << 30) && g.plane < ((int64_t)1 << 28);
 }
 
 hipError_t launch3_fused(int scheme, int layout, int prec, const KParams3& p, const void* src, void* dst, hipStream_t s)

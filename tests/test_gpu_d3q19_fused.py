@@ -48,6 +48,13 @@ def test_two_updates_per_launch_bitwise(nx, ny, nz):
              lambda k: [("NPTL", "stream"), ("NPTL", "blocked"), ("AA", "blocked" if k % 2 else "stream")])
 
 
+# the fewest rows, planes and columns of a row that do two updates per launch
+@pytest.mark.parametrize("nx,ny,nz", [(700, 6, 360), (811, 630, 3), (24, 250, 251), (16, 320, 300)])
+def test_two_updates_per_launch_bitwise_thin(nx, ny, nz):
+    _compare(nx, ny, nz, "fp32", [AXES[1], AXES[4]],
+             lambda k: [("NPTL", "blocked"), ("AA", "blocked")] + ([("NPTL", "stream"), ("AA", "stream")] if nx > 23 else []))
+
+
 # from 4 million nodes on, x axis not periodic
 @pytest.mark.parametrize("precision", [p for p in ALL_PRECISIONS if p != "fp32"])
 def test_two_updates_per_launch_bitwise_16_bit(precision):
