@@ -285,12 +285,12 @@ int32_t lbm_bytes_per_update(int32_t precision);
  * slot and space in the HBM budget are free (arrival order, later requests
  * may pass one that does not fit yet), kept resident, and advanced together:
  * every bundle is one replay of a captured HIP graph of `bundle_steps`
- * updates of every resident request by a persistent batched kernel, up to four
- * updates per launch (two-lattice pull, same arithmetic as lbm_step, so a
- * request's result is independent of the mix).  While a request with the
- * Neumann inlet, or less than four rows and a periodic y axis, is resident, all
- * advance by one update per launch.  A request stops at exactly its step
- * count; its rho and u are then read back and its memory freed.
+ * updates of every resident request by a persistent batched kernel (two-lattice
+ * pull, same arithmetic as lbm_step, so a request's result is independent of
+ * the mix).  A launch does up to four updates, but one while few nodes are
+ * resident or any request with the Neumann inlet, or with less than four rows
+ * and a periodic y axis.  A request stops at exactly its step count; its rho
+ * and u are then read back and its memory freed.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_server lbm_server;
 

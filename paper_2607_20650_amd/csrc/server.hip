@@ -552,16 +552,23 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
     int32_t nw = 0;
     InFlight b;
     int64_t res_bytes = 0;
-    // several updates per launch unless a resident request needs single ones;
-    // strips of as many rows as make about 2560 items (2.5 wavefronts per
-    // SIMD): fewer rows cost recomputed ones, more leave the chip idle
+    // Several updates per launch unless a resident request needs single ones or
+    // all are small: a launch of four updates takes 28 us (FP32) to 43 us
+    // (FP16C-SR) by its chain of rows alone, four of single updates 20 to 29 us
+    // (per update, single updates : several: 64 x 64 FP32 5.0 : 7.4, FP16C-SR 7.2 :
+    // 10.9; 500 x 400 FP32 7.6 : 8.7; 16 of 128 x 128 FP32 12.9 : 10.1; 900 x 600
+    // FP16S 11.2 : 11.3, FP16S-SR 13.4 : 13.6; 48 of 128 x 128 23.2 : 21.7).
+    // Strips of as many rows as make about 2560 items (2.5 wavefronts per SIMD):
+    // fewer rows cost recomputed ones, more leave the chip idle
     bool fused = true;
-    int64_t strip_rows = 0;
+    int64_t strip_rows = 0, nodes = 0;
     for (const Request* r : s->slot_req)
         if (r) {
             fused = fused && !r->single;
+            nodes += r->kp.g.nx * r->kp.g.ny;
             strip_rows += r->strips * r->kp.g.ny;
         }
+    fused = fused && nodes >= (s->elem == 4 ? 230000 : 550000);
     const int32_t rows = (int32_t)std::min<int64_t>(std::max<int64_t>(strip_rows / 2560, BATCH_MIN_ROWS), 64);
     for (int k = 0; k < s->max_slots; ++k) {
         Request* r = s->slot_req[k];

@@ -287,6 +287,35 @@ void readout_from_another_device()
     }
 }
 
+// Served requests of few nodes run single updates, more of them several per
+// launch, and a request may see both.
+void served_by_load()
+{
+    Stream* stream = new Stream();
+    lbm_server* s = nullptr;
+    expect(lbm_server_create(1 << 28, 4, 10, 0, 0, stream, &s) == LBM_OK, "server");
+    const std::vector<uint8_t> flags(1000 * 400, 0);
+    lbm_bc bc{};
+    bc.x_axis = bc.y_axis = LBM_CLOSED;
+    bc.rho0 = 1.0;
+    uint64_t id[2];
+    lbm_grid small{100, 100, S_NPTL, 0, 0, 0, 0}, large{1000, 400, S_NPTL, 0, 0, 0, 0};
+    lbm_server_submit(s, &small, flags.data(), 0.8, &bc, 35, &id[0]);
+    lbm_server_run_bundle(s);
+    expect(dev.singles == 10 && dev.fused == 0, "a small request alone");
+    lbm_server_submit(s, &large, flags.data(), 0.8, &bc, 12, &id[1]);
+    lbm_server_run_bundle(s);
+    lbm_server_run_bundle(s);
+    expect(dev.singles == 10 && dev.fused == 6, "beside a large one");
+    lbm_server_run_bundle(s);
+    expect(dev.singles == 20 && dev.fused == 6, "alone again");
+    lbm_server_run_bundle(s);
+    int32_t status[2], n = 0;
+    expect(lbm_server_poll(s, id, status, 2, &n) == LBM_OK && n == 2, "both finished");
+    lbm_server_destroy(s);
+    delete stream;
+}
+
 // The first served request that needs single updates makes the serving loop
 // capture one bundle, not one per grid size.
 void served_single_updates()
@@ -492,6 +521,7 @@ const std::map<std::string, void (*)()> SCENARIOS = {
     {"captured_3d", captured_3d},
     {"graphs_after_capture", graphs_after_capture},
     {"readout_from_another_device", readout_from_another_device},
+    {"served_by_load", served_by_load},
     {"served_single_updates", served_single_updates},
     {"calls_of_one_update", calls_of_one_update},
     {"given_back", given_back},

@@ -32,7 +32,7 @@ def scenarios(tmp_path_factory):
 @pytest.mark.parametrize("name", ["captured_readout", "captured_load", "eager_before_replay", "captured_3d",
                                   "graphs_after_capture", "calls_of_one_update", "given_back", "given_back_to_others",
                                   "given_back_across_threads", "spare_memory_is_bounded", "readout_from_another_device",
-                                  "served_single_updates"])
+                                  "served_single_updates", "served_by_load"])
 def test_scenario(scenarios, name):
     r = subprocess.run([scenarios, name], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout[:2000]
