@@ -271,8 +271,8 @@ void readout_from_another_device()
     for (int first : {0, 1}) {
         plan = FusedPlan{8, 1, 0};
         (void)hipSetDevice(0);
-        Sim a(S_NPTL, 1024, 400);
-        std::vector<float> f(9 * 1024 * 400, 7.0f);
+        Sim a(S_NPTL, 1024, 600); // rho alone goes through the chunks
+        std::vector<float> f(9 * 1024 * 600, 7.0f);
         expect(lbm_set_state(a.c, f.data(), 0) == LBM_OK, "load");
         for (int k = 0; k < 3; ++k) {
             (void)hipSetDevice(k == 0 ? first : 1 - first);
