@@ -1028,9 +1028,11 @@ __device__ __forceinline__ void split_index3(const Geometry3& g, int64_t m, int6
 }
 
 // Incoming populations of an updated node of type t: regular nodes read fixed
-// (or, on a periodic border, wrapped) offsets, irregular ones look up their
-// neighbours' types.  Looking them up for every node took 590 us for the
-// fields of a 256^3 grid.
+// (or, on a periodic border, wrapped) offsets, irregular ones their link word
+// or, without one, their neighbours' types.  Looking up the types for every node
+// took 590 us for the fields of a 256^3 grid.  (Without link words, one path for
+// all nodes of a wavefront that has an irregular one would gain 2 us on a 33 x 20
+// x 20 grid, but the fields of a 128^3 AA duct took 189 us that way, 90 this way.)
 template <int L, int S, class T>
 __device__ __forceinline__ void gather_typed3(const KParams3& p, const T* __restrict__ lat, int64_t x, int64_t y,
                                               int64_t z, int64_t n, uint8_t t, float* f)
