@@ -11,10 +11,10 @@ device synchronisation and timed with HIP events on the library's stream.
 
 Also reported on the same JSON line:
   * every scheme x layout x precision variant (median of repeated runs),
-  * roofline of the dominant update kernel (algorithmic bytes per update, one
-    read and one write of the lattice, over the measured time per update,
-    against the 8 TB/s HBM peak; a launch of several updates moves the lattice
-    once for all of them, so this can exceed the peak),
+  * roofline of the dominant update kernel: for a launch of several updates the
+    vector instructions of its collisions against the chip's issue rate, beside
+    the bytes it moves (one read and one write of the lattice per launch)
+    against the 8 TB/s HBM peak; for single updates that rate alone,
   * the FP64 CPU oracle timed on the host cores on a bounded sample,
   * an off-cache reference grid and the 2^31-node memory-limit grid,
   * batched-serving latency and throughput when the serving engine is built.
@@ -35,8 +35,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+# Vector instructions: 256 CUs x 64 lanes x 2.4 GHz, in 10^12 lane instructions
+# per second, and those of one FP32 collision without loads, stores and streaming
+VALU_PEAK_T = 39.3
+VALU_PER_UPDATE = {9: 77, 19: 165}
 SCHEMES = ["LPTL", "NPTL", "PUSH", "NPOL", "NSOL", "AA"]
 LAYOUTS = ["stream", "bundle", "collision"]
+TWO_LATTICE = ("LPTL", "NPTL", "PUSH")
+FUSED = 8  # most updates per launch of k_fused on large FP32 grids (lattices up to 1.5 GiB where the scheme needs one)
 PRECISIONS = ["fp32", "fp16s", "fp16sr", "fp16c", "fp16csr"]
 GOLDEN_DIR = os.path.join(ROOT, "tests", "golden")
 MALL_BYTES = 256 * 2 ** 20  # MI355X Infinity Cache
@@ -78,27 +84,38 @@ def accuracy(lbm, sc, scheme, layout, prec, g):
 
 
 def kernel_name(scheme, layout, precision, tile_x):
-    """Update kernel the library launches for a variant on this workload (the
-    dispatch rules of the HIP sources: FP32 and FP16S(-SR) do several updates
-    per launch in k_fused; FP16C lattices that fit the Infinity Cache take the
-    schemes' own kernels, where one-wavefront-wide NPOL tiles take the lean
-    kernel and 64-wide collision-layout tiles of the two-lattice pull, of AA
-    and of the FP32 push the LDS-staged ones)."""
-    if not precision.startswith("fp16c"):
+    """Update kernel the library launches for a variant on the 4096 x 1024
+    workload (the dispatch rules of the HIP sources: several updates per launch
+    in k_fused, but for FP16C in NPTL and in stream AA and PUSH, whose lattices
+    fit the Infinity Cache here and which take the schemes' own kernels: the
+    64-wide collision-layout tiles of the two-lattice pull the LDS-staged
+    one)."""
+    fast = scheme == "NPTL" or (scheme in ("AA", "PUSH") and layout == "stream")
+    if not (precision.startswith("fp16c") and fast):
         return "k_fused"
-    staged = layout == "collision" and tile_x == 64
-    if scheme == "NPOL":
-        return "k_npol64" if tile_x == 64 else "k_npol"
-    if scheme == "NSOL":
-        return "k_nsol"
     if scheme == "AA":
-        # alternate launches, same bytes each
-        return "k_aa_even_aos+k_aa_odd_aos" if staged else "k_aa_even+k_aa_odd"
-    if scheme == "NPTL" and staged:
+        return "k_aa_even+k_aa_odd"  # alternate launches, same bytes each
+    if scheme == "NPTL" and layout == "collision" and tile_x == 64:
         return "k_nptl_aos"
-    if scheme == "PUSH" and staged and precision == "fp32":
-        return "k_push_staged"
-    return {"LPTL": "k_lptl", "NPTL": "k_nptl", "PUSH": "k_push"}[scheme]
+    return {"NPTL": "k_nptl", "PUSH": "k_push"}[scheme]
+
+
+def fused_roofline(mlups, updates, q, elem=4):
+    """Roofline of a kernel that does `updates` updates of a D2Q9 (q = 9) or
+    D3Q19 (q = 19) lattice per launch: useful instructions against the issue
+    rate, and the lattice's bytes, moved once per launch, against HBM."""
+    t = mlups * 1e6 * VALU_PER_UPDATE[q] / 1e12
+    gbs = mlups * 1e6 * 2 * q * elem / updates / 1e9
+    return {"bound": "valu", "achieved": round(t, 3), "peak": VALU_PEAK_T, "unit": "10^12 lane instructions/s",
+            "frac": round(t / VALU_PEAK_T, 4), "instructions_per_update": VALU_PER_UPDATE[q],
+            "updates_per_launch": updates, "hbm_gbs": round(gbs, 1), "hbm_frac": round(gbs / HBM_PEAK_GBS, 4)}
+
+
+def hbm_roofline(mlups, q, elem=4):
+    """Roofline of single updates: the lattice read and written once each."""
+    gbs = mlups * 1e6 * 2 * q * elem / 1e9
+    return {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(gbs / HBM_PEAK_GBS, 4)}
 
 
 def csrc_digest() -> str:
@@ -248,7 +265,8 @@ def hbm_reference(torch, lbm, workloads, log, headline, steps=100):
         mlups = sc.nx * sc.ny * steps / (ms * 1e-3) / 1e6
         gbs = mlups * 1e6 * 72 / 1e9
         out["variants"][f"{scheme}/{layout}/fp32"] = {
-            "mlups": round(mlups, 1), "algorithmic_gbs": round(gbs, 1), "frac_of_8tbs": round(gbs / HBM_PEAK_GBS, 4),
+            "mlups": round(mlups, 1), "algorithmic_gbs": round(gbs, 1),
+            "updates_per_launch": FUSED if scheme in TWO_LATTICE else 1,
             "update_us": round(ms * 1e3 / steps, 2), "device_gb": round(lat_gb, 2)}
         log(f"hbm reference {sc.nx}x{sc.ny} {scheme}/{layout}/fp32: {mlups:.0f} MLUPS, {gbs:.0f} GB/s")
     return out
@@ -325,7 +343,7 @@ def d3q19_sweep(torch, lbm, workloads, log, steps=100, reps=5):
         bpn = 2 * 19 * (4 if prec == "fp32" else 2)
         key = f"{scheme}/{layout}/{prec}"
         out["variants"][key] = {"mlups_median": round(mlups, 1), "gbs": round(mlups * 1e6 * bpn / 1e9, 1),
-                                "hbm_frac": round(mlups * 1e6 * bpn / 1e9 / HBM_PEAK_GBS, 4)}
+                                "updates_per_launch": 2 if layout != "collision" and prec == "fp32" else 1}
         log(f"d3q19 {key:24s} {mlups:10.1f} MLUPS  {mlups * 1e6 * bpn / 1e9:7.1f} GB/s")
     # memory limit: 1024^3 nodes (2^30) in place, 81.6 GB of FP32 populations
     big = workloads.sphere_array(n=1024, radius=160.0)
@@ -339,14 +357,15 @@ def d3q19_sweep(torch, lbm, workloads, log, steps=100, reps=5):
                            "gbs": round(mlups * 1e6 * 152 / 1e9, 1), "lattice_gb": round(nb * 76 / 1e9, 1)}
     log(f"d3q19 memory limit {big.name} AA/stream/fp32: {mlups:.0f} MLUPS, {mlups * 152 / 1e3:.0f} GB/s")
     del big
-    # roofline of the fastest FP32 variant: its dominant kernels are HBM bound
+    # roofline of the fastest FP32 variant
     best = max((k for k in out["variants"] if k.endswith("/fp32")), key=lambda k: out["variants"][k]["mlups_median"])
     scheme, layout, _ = best.split("/")
-    staged = layout == "collision"  # one update per launch
-    kern = ("k3_aa_even+k3_aa_odd" if scheme == "AA" else "k3_pull") if staged else "k3_fused"
     v = out["variants"][best]
-    out["roofline"] = {"bound": "hbm", "variant": best, "achieved": v["gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                       "frac": v["hbm_frac"], "bytes_per_node": 152,
+    several = v["updates_per_launch"] > 1
+    kern = "k3_fused" if several else ("k3_aa_even+k3_aa_odd" if scheme == "AA" else "k3_pull")
+    out["roofline"] = {**(fused_roofline(v["mlups_median"], v["updates_per_launch"], 19) if several
+                          else hbm_roofline(v["mlups_median"], 19)),
+                       "variant": best, "bytes_per_node": 152,
                        "traffic": stored_traffic(f"{kern}/{layout}/fp32"), "kernel": f"{kern}/{layout}/fp32"}
     return out
 
@@ -441,13 +460,13 @@ def main():
               for m in ("copy", "copy_nt") for sz in (1, 4)}
     copy_gbs = max(probes.values())
     working_set = info["device_bytes"]
-    roofline = {"bound": "valu" if "k_fused" in kernel_key else "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": kernel_key, "bytes_per_update": bpu * cells, "update_us": round(update_s * 1e6, 2),
-                "working_set_mb": round(working_set / 2 ** 20, 1),
+    # evenly filled launches of at most FUSED updates: 50 per graph are 7 launches
+    per_launch = info["bundle"] / -(-info["bundle"] // FUSED)
+    roofline = {**fused_roofline(value, per_launch, 9), "traffic": traffic, "kernel": kernel_key,
+                "bytes_per_update": bpu * cells, "update_us": round(update_s * 1e6, 2),
+                "algorithmic_gbs": round(achieved, 1), "working_set_mb": round(working_set / 2 ** 20, 1),
                 "cache_resident": working_set <= MALL_BYTES,
-                "copy_probe_gbs": round(copy_gbs, 1), "copy_probes": probes,
-                "frac_of_copy_probe": round(achieved / copy_gbs, 4)}
+                "copy_probe_gbs": round(copy_gbs, 1), "copy_probes": probes}
     log(f"copy probes: {probes}")
 
     # ---- 16-bit storage: speed of the fastest variant of each format, and its
@@ -463,7 +482,7 @@ def main():
         s16, l16 = best(prec)
         v16 = variants[f"{s16}/{l16}/{prec}"]["mlups_median"]
         ent = {"variant": f"{s16}/{l16}", "mlups": v16, "ratio_vs_fp32": round(v16 / v32, 3),
-               "hbm_frac": round(v16 * 1e6 * 36 / 1e9 / HBM_PEAK_GBS, 4)}
+               "algorithmic_gbs": round(v16 * 1e6 * 36 / 1e9, 1)}
         if golden is not None:
             ent["velocity_error_after_%d" % int(golden["steps"])] = accuracy(lbm, sc, s16, l16, prec,
                                                                              golden)["velocity_error"]
@@ -484,13 +503,14 @@ def main():
     if hbm_ref:
         hv = hbm_ref["variants"][f"{scheme}/{layout}/fp32"]
         bk = max(hbm_ref["variants"], key=lambda k: hbm_ref["variants"][k]["mlups"])
-        roofline_offcache = {
-            "bound": "hbm", "workload": hbm_ref["workload"], "variant": f"{scheme}/{layout}/fp32",
-            "achieved": hv["algorithmic_gbs"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": hv["frac_of_8tbs"],
-            "update_us": hv["update_us"], "frac_of_copy_probe": round(hv["algorithmic_gbs"] / copy_gbs, 4),
-            "best_variant": bk, "best_achieved": hbm_ref["variants"][bk]["algorithmic_gbs"],
-            "best_frac": hbm_ref["variants"][bk]["frac_of_8tbs"],
-            "best_frac_of_copy_probe": round(hbm_ref["variants"][bk]["algorithmic_gbs"] / copy_gbs, 4)}
+        bv = hbm_ref["variants"][bk]
+
+        def off(v):
+            n = v["updates_per_launch"]
+            return fused_roofline(v["mlups"], n, 9) if n > 1 else hbm_roofline(v["mlups"], 9)
+        roofline_offcache = {**off(hv), "workload": hbm_ref["workload"], "variant": f"{scheme}/{layout}/fp32",
+                             "update_us": hv["update_us"], "best_variant": bk, "best": off(bv),
+                             "copy_probe_gbs": round(copy_gbs, 1)}
     porous = None if args.no_sweep else porous_block(torch, lbm, workloads, variants, log)
     channel = channel_block(lbm, workloads, log)
     mem_limit = None if (args.no_sweep or args.no_memory_limit) else memory_limit(torch, lbm, workloads, log)
@@ -515,7 +535,7 @@ def main():
         "config": {"workload": "karman-4096x1024-re100", "nx": sc.nx, "ny": sc.ny, "scheme": scheme,
                    "layout": layout, "storage": "fp32", "tile": [info["tile_x"], info["tile_y"]],
                    "graph_bundle": info["bundle"]},
-        "hbm_frac": round(achieved / HBM_PEAK_GBS, 4),
+        "hbm_frac": roofline["hbm_frac"],
         "mlups_fluid": round(value * updated / cells, 1),
         "roofline": roofline,
         "roofline_offcache": roofline_offcache,

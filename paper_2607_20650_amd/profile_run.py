@@ -6,7 +6,8 @@ extension with --workload sphere-array-256) plus a copy kernel of known size
     rocprofv3 --pmc FETCH_SIZE -d <dir> -- python -m paper_2607_20650_amd.profile_run
     rocprofv3 --pmc WRITE_SIZE -d <dir> -- python -m paper_2607_20650_amd.profile_run
 
-Updates are launched one by one (no graphs) so every dispatch is visible.
+Updates are launched one by one (no graphs) so every dispatch is visible; with
+--several N in launches of N updates each (D2Q9).
 """
 from __future__ import annotations
 
@@ -21,6 +22,7 @@ def main():
     ap.add_argument("--precision", default="fp32")
     ap.add_argument("--workload", default="karman", choices=["karman", "channel-16000x8000", "sphere-array-256"])
     ap.add_argument("--steps", type=int, default=20)
+    ap.add_argument("--several", type=int, default=0, help="updates per launch (a number the grid's plan allows)")
     ap.add_argument("--probe-bytes", type=int, default=1 << 30)
     args = ap.parse_args()
 
@@ -47,9 +49,9 @@ def main():
     print(f"profile_run: {args.workload} {sc.nx}x{sc.ny} {args.scheme}/{args.layout}/{args.precision} "
           f"{args.steps} updates", flush=True)
     with lbm.Simulation.from_scenario(sc, scheme=args.scheme, layout=args.layout, precision=args.precision,
-                                      bundle=0) as sim:
+                                      bundle=args.several) as sim:
         for k in range(args.steps):
-            sim.step(1)
+            sim.step(args.several or 1)
         sim.sync()
         st, d = sim.diag()
         print(f"profile_run: updates done, diag status {st}, mass {d[0]:.6f}", flush=True)
