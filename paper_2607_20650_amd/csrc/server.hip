@@ -125,8 +125,10 @@ struct lbm_server {
     // captured bundles per persistent grid size: the full grid (resident
     // blocks on the device) and smaller ones down to 1/32 of it, so that a
     // bundle over few work items launches few blocks; [1]: several updates per
-    // launch, [0]: one (each captured when a request that needs it is resident)
-    static constexpr int NGRIDS = 6;
+    // launch, [0]: one, in two sizes only (50 launches to capture, which cost
+    // more than the blocks that end at once: one 256 x 256 request 5.7 us per
+    // update on the full grid, 5.6 on an eighth)
+    static constexpr int NGRIDS = 6, FEW = 4;
     hipGraph_t graph[2][NGRIDS] = {};
     hipGraphExec_t gexec[2][NGRIDS] = {};
     int grid_blocks[2][NGRIDS] = {};
@@ -439,11 +441,12 @@ lbm_status lbm_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_
     if (hipMemcpy(s->d_slots, s->h_slots[0], sizeof(SlotDesc) * max_slots, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(s->d_nwork, s->h_nwork[0], 2 * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess)
         return cleanup(LBM_EDEVICE, "descriptor upload failed");
-    for (int v = 0; v < lbm_server::NGRIDS; ++v) {
-        for (bool fused : {false, true})
+    for (bool fused : {false, true})
+        for (int v = 0; v < lbm_server::NGRIDS; ++v) {
             s->grid_blocks[fused][v] = std::max(1, batched_blocks(layout, precision, fused) >> v);
-        if (!capture_bundle(s, true, v)) return cleanup(LBM_EDEVICE, "bundle capture failed");
-    }
+            if (!fused && v != 0 && v != lbm_server::FEW) continue;
+            if (!capture_bundle(s, fused, v)) return cleanup(LBM_EDEVICE, "bundle capture failed");
+        }
     *out = s;
     return LBM_OK;
 }
@@ -606,11 +609,14 @@ lbm_status lbm_server_run_bundle(lbm_server* s)
         if (!s->flight.empty()) return finish_oldest(s, true);
         return LBM_OK;
     }
-    // the smallest grid with at least one block per work item (four strips)
+    // the smallest captured grid with at least one block per work item (four
+    // strips)
     const int32_t need = fused ? (nw + 3) / 4 : nw;
     int v = 0;
-    while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[fused][v + 1] >= need) ++v;
-    if (!s->gexec[fused][v] && !capture_bundle(s, fused, v)) return s->fail(LBM_EDEVICE, "bundle capture failed");
+    if (fused)
+        while (v + 1 < lbm_server::NGRIDS && s->grid_blocks[1][v + 1] >= need) ++v;
+    else if (s->grid_blocks[0][lbm_server::FEW] >= need)
+        v = lbm_server::FEW;
     // the bundle's arena region: staged flags of the admitted requests, then
     // the results of the finishing ones
     int64_t up_bytes = 0;
