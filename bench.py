@@ -237,7 +237,8 @@ def memory_limit(torch, lbm, workloads, log, steps=50):
             mlups = nx * ny * steps / (ms * 1e-3) / 1e6
             gbs = mlups * 1e6 * 72 / 1e9
             out[f"plate-{nx}x{ny}/{scheme}/{layout}/fp32"] = {
-                "mlups": round(mlups, 1), "algorithmic_gbs": round(gbs, 1), "frac_of_8tbs": round(gbs / HBM_PEAK_GBS, 4),
+                "mlups": round(mlups, 1), "algorithmic_gbs": round(gbs, 1),
+                "updates_per_launch": FUSED if scheme in TWO_LATTICE else 1,
                 "device_gb": round(dev_gb, 1), "steps": steps}
             log(f"memory limit {nx}x{ny} {scheme}/{layout}/fp32: {mlups:.0f} MLUPS, {gbs:.0f} GB/s, "
                 f"{dev_gb:.1f} GB on the device")
