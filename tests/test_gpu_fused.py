@@ -148,3 +148,36 @@ def test_captured_steps_replay(scheme):
             sim.step(34)
             ref.step(34)
             assert np.array_equal(sim.populations(), ref.populations()), (scheme, k)
+
+
+def test_spare_memory_goes_back():
+    """A server pool that cannot be had takes the second lattices and link words
+    of the simulations with it; they go on in place, bit for bit."""
+    from paper_2607_20650_amd.lbm import ENOMEM, LbmError, Server, Simulation, Simulation3
+    flags, flags3 = W.random_flags(2311, 701, 0.1, 4), W.random_flags3(130, 125, 95, 0.1, 4)
+    kw = dict(u_in=(0.05, 0.01), u0=(0.02, 0.0))
+    kw3 = dict(u_in=(0.05, 0.01, 0.0), u0=(0.02, 0.0, 0.0), scheme="AA")
+    axes3 = (INFLOW_OUTFLOW, CLOSED, CLOSED)
+    refs = [Simulation(flags, 0.8, INFLOW_OUTFLOW, CLOSED, scheme="NPTL", bundle=0, **kw),
+            Simulation3(flags3, 0.8, *axes3, **kw3)]
+    sims = [Simulation(flags, 0.8, INFLOW_OUTFLOW, CLOSED, scheme=s, **kw) for s in ("AA", "NPOL", "NSOL")]
+    sim3 = Simulation3(flags3, 0.8, *axes3, **kw3)
+    held = [s.info()["device_bytes"] for s in sims]
+    for s in sims + [sim3]:
+        s.step(6)  # one launch (two-dimensional): the state is in the second lattice
+    with pytest.raises(LbmError) as e:
+        Server(1 << 45)
+    assert e.value.status == ENOMEM
+    for s, before in zip(sims, held):
+        assert s.info()["device_bytes"] < before
+    for n in (1, 9, 16):
+        for s in sims + [sim3]:
+            s.step(n)
+    refs[0].step(32)
+    for _ in range(32):
+        refs[1].step(1)
+    for s in sims:
+        assert np.array_equal(s.populations(), refs[0].populations()), s.scheme
+    assert np.array_equal(sim3.populations(), refs[1].populations())
+    for s in sims + refs + [sim3]:
+        s.close()
