@@ -24,7 +24,7 @@ CSRC = os.path.join(ROOT, "paper_2607_20650_amd", "csrc")
 def scenarios(tmp_path_factory):
     exe = str(tmp_path_factory.mktemp("host_model") / "scenarios")
     subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", MODEL, "-I", CSRC, "-I", os.path.join(ROOT, "include"),
-                    "-x", "c++", os.path.join(CSRC, "context.hip"), os.path.join(CSRC, "context3.hip"), os.path.join(CSRC, "server.hip"),
+                    "-x", "c++", *(os.path.join(CSRC, f) for f in ("context.hip", "context3.hip", "server.hip")),
                     os.path.join(MODEL, "model.cpp"), os.path.join(MODEL, "scenarios.cpp"), "-o", exe], check=True)
     return exe
 

@@ -70,7 +70,8 @@ def test_long_grids_of_few_rows(plan_of, nx, ny, scheme, precision, several):
 @pytest.mark.parametrize("nx,ny,nz,axis,several", [
     (201, 97, 85, PERIODIC, True), (201, 97, 85, INFLOW_OUTFLOW, True), (128, 96, 96, INFLOW_OUTFLOW, False),
     (900, 600, 3, PERIODIC, True), (900, 900, 2, PERIODIC, False), (500, 8, 420, INFLOW_OUTFLOW, True),
-    (700, 4, 600, INFLOW_OUTFLOW, False), (24, 300, 250, PERIODIC, True), (128, 128, 128, PERIODIC, None), (64, 256, 256, PERIODIC, False), (128, 128, 128, INFLOW_OUTFLOW, True),
+    (700, 4, 600, INFLOW_OUTFLOW, False), (24, 300, 250, PERIODIC, True), (128, 128, 128, PERIODIC, None),
+    (64, 256, 256, PERIODIC, False), (128, 128, 128, INFLOW_OUTFLOW, True),
     (256, 256, 256, PERIODIC, True)])
 def test_two_d3q19_updates_per_launch_where_they_are_faster(plans, nx, ny, nz, axis, several, scheme, layout):
     if several is None:
